@@ -16,8 +16,8 @@ constexpr int kSpecQuantile = 65;    // T_spec: sampled key of rank ceil(65 / 20
 constexpr int kGuessMaxK = 2048;     // the quantile's denominator (the largest K)
 
 // Sample stride and sample count for a Top-K of size K.
-DEV int guess_stride(int K) { return (K + kGuessSamples - 1) / kGuessSamples; }
-DEV int guess_count(int K) {
+__host__ DEV int guess_stride(int K) { return (K + kGuessSamples - 1) / kGuessSamples; }
+__host__ DEV int guess_count(int K) {
     const int st = guess_stride(K);
     return (K + st - 1) / st;
 }

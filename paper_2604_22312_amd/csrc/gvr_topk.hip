@@ -131,27 +131,40 @@ static_assert((kBins & (kBins - 1)) == 0 && (kRefBins & (kRefBins - 1)) == 0 && 
                   (kGuessBins & (kGuessBins - 1)) == 0, "bin counts are powers of two");
 static_assert(kSmall * 4 <= kRefBins, "refine candidates over the histogram");
 
-struct Params {
+// What a workgroup needs before its first loads, as scalar kernel arguments:
+// the command processor preloads them into SGPRs (the build asks for 14
+// dwords), so the addresses of the row, its length and the guess follow from
+// a few scalar operations with no argument load and no division (the host
+// sends the split as a magic factor). Start to first slab load issued for one 8K
+// row: 1.8 -> 1.0 us against loading one argument struct and dividing.
+struct Head {
     const float* scores;
-    int64_t ld;
-    const int32_t* row_len;
-    const int32_t* prev;
+    const int32_t* row_len;   // or NULL
+    const int32_t* prev;      // or NULL
+    int32_t ld;
+    int32_t K;
+    int32_t rows;        // rows of this launch
+    int32_t chunk;       // gridDim.x / 8: consecutive (row, part) slots per XCD
+    uint32_t s_magic;    // ceil(2^32 / S), S workgroups per row (unused for S = 1)
+    int32_t capacity;    // C
+    uint32_t geo;        // S | scatter << 5 | sample stride << 6 | samples << 10 | flags from bit 19
+};
+constexpr int kGeoScatter = 5, kGeoStride = 6, kGeoSamples = 10;
+constexpr int kGeoFromIndexer = 19;   // the guess statistics come from the indexer (Params::gstats)
+constexpr int kGeoTimed = 20;         // row stats are asked for (Params::stats)
+constexpr int kGeoSecant = 21;        // the paper's Phase 2 (secant counting passes) instead of the speculative pass
+static_assert(kMaxParts < 32 && kGuessMaxK / kGuessSamples < 16 && kGuessSamples < 512, "fields of Head::geo");
+
+struct Params {
     int32_t* out;
     gvr_row_stats* stats;
-    int32_t K;
-    int32_t capacity;    // C
-    int32_t rows;        // rows of this launch
-    int32_t parts;       // S: workgroups per row
-    int32_t chunk;       // gridDim.x / 8: consecutive (row, part) slots per XCD
-    int32_t scatter;     // 1: slot = blockIdx.x (parts of a row on different XCDs)
-    int32_t secant;      // 1: the paper's Phase 2 (secant counting passes) instead of the speculative pass
     int32_t paper_refine; // 1: the paper's Phase 4 (min/max, histogram, snap iterations) instead of refine_emit
     uint64_t* arrivals;  // [rows] parts that finished the speculative pass (S > 1), per XCD above
                          // bit 16; 0 between calls
     int32_t* part_count; // [rows][S] f(threshold) of each part, bit 31 = a wave list overflowed
     uint32_t* part_thresh; // [rows][S] threshold of each part's list (T_spec, the same in every part)
     int32_t* part_hist;  // [rows][S][kRefBins1] each part's first refine level over [T_spec, pmax]
-    const int32_t* gstats; // or NULL: GuessStats words of every row (row stride K), from the indexer
+    const int32_t* gstats; // GuessStats words of every row (row stride K), from the indexer
     int32_t ordered_merge; // arrival counter updated with agent-scope release / acquire
     uint64_t* part_list; // [rows][S][kPartCap] (fp32 bits | index << 32) of each part
 };
@@ -907,24 +920,34 @@ constexpr uint32_t kKeyZeroBits = 0xFFFFFFFFu;
 
 DEV uint64_t pack_entry(uint32_t bits, uint32_t idx) { return (uint64_t)bits | ((uint64_t)idx << 32); }
 
+// v / S by the host's magic factor: exact for v < 2^28 and S <= 16.
+DEV int div_parts(int v, int S, uint32_t magic) { return S == 1 ? v : (int)__umulhi((uint32_t)v, magic); }
+
 template <bool GUESS, int NW, bool NT>
-DEV void topk_body(const Params& p) {
+DEV void topk_body(const Head& hd, const Params& p) {
     __shared__ Smem<NW> sm;
     using W = Shape<NW>;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int S = p.parts;
+    const int S = (int)(hd.geo & 31u);
+    const int K = hd.K;
     // Slot (row, part) of this workgroup: consecutive slots on one XCD, so the
     // parts of a row share an L2 (scatter: the plain order, for tests of the
     // cross-XCD path).
-    const int slot = p.scatter ? (int)blockIdx.x : (int)(blockIdx.x % kXcds) * p.chunk + (int)(blockIdx.x / kXcds);
-    const int row_i = slot / S;
+    const int slot = ((hd.geo >> kGeoScatter) & 1u)
+                         ? (int)blockIdx.x
+                         : (int)(blockIdx.x % kXcds) * hd.chunk + (int)(blockIdx.x / kXcds);
+    const int row_i = div_parts(slot, S, hd.s_magic);
     const int part = slot - row_i * S;
-    if (row_i >= p.rows) return;   // padding slot of the XCD-aligned grid
+    if (row_i >= hd.rows) return;   // padding slot of the XCD-aligned grid
     const int64_t row = row_i;
+    // Row length through the scalar cache (row is wave-uniform): it does not
+    // wait behind vector loads, nor they behind it.
+    int len = hd.ld;
+    if (hd.row_len) len = *(const __attribute__((address_space(4))) int32_t*)(hd.row_len + row);
     // Phase stamps are taken only when row stats are asked for: a clock read
     // is a scalar memory operation, and the next LDS wait would wait for it.
-    const bool timed = p.stats != nullptr;
+    const bool timed = (hd.geo >> kGeoTimed) & 1u;
     auto tstamp = [&]() -> int64_t { return timed ? stamp() : (int64_t)0; };
     const int64_t t0 = tstamp();
 
@@ -932,36 +955,33 @@ DEV void topk_body(const Params& p) {
     // kGuessSamples of them). The sample indices go out with the row length;
     // the gathers that depend on them are the only serial memory latency
     // before T_spec, and the part's first slabs are in flight meanwhile.
-    const int st_g = guess_stride(p.K);
-    const int m_g = guess_count(p.K);
-    int pq[4] = {-1, -1, -1, -1};
-    int gw[5] = {-1, 0, -1, 0, 0};   // the indexer's GuessStats words of this row (gvr_indexer_topk)
-    if (GUESS && p.prev && wave == 0) {
-        if (p.gstats) {
-            const int32_t* g = p.gstats + row * (int64_t)p.K;
+    const int m_g = (int)((hd.geo >> kGeoSamples) & 511u);
+    const bool from_indexer = GUESS && ((hd.geo >> kGeoFromIndexer) & 1u);   // GuessStats words instead (gvr_indexer_topk)
+    int pq[4];   // loaded and used by wave 0 only
+    if (GUESS && hd.prev && wave == 0 && !from_indexer) {
+        const int st_g = (int)((hd.geo >> kGeoStride) & 15u);
+        const int32_t* pv = hd.prev + row * (int64_t)K;
 #pragma unroll
-            for (int c = 0; c < 5; ++c) gw[c] = g[c];
-        } else {
-            const int32_t* pv = p.prev + row * (int64_t)p.K;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int i = lane + 64 * c;
-                if (i < m_g) pq[c] = pv[i * st_g];
-            }
-        }
+        for (int c = 0; c < 4; ++c) pq[c] = pv[min(lane + 64 * c, m_g - 1) * st_g];
     }
-    // Row length through the scalar cache (row is wave-uniform): it does not
-    // wait behind the vector loads above.
-    int64_t n64 = p.row_len ? (int64_t)__builtin_amdgcn_readfirstlane(
-                                  *(const __attribute__((address_space(4))) int32_t*)(p.row_len + row))
-                            : p.ld;
-    n64 = n64 < 0 ? 0 : (n64 > p.ld ? p.ld : n64);
-    const int n = (int)n64;
-    const int K = p.K;
-    const int cap = p.capacity;
-    const float* x = p.scores + row * p.ld;
+    int gw[5];   // likewise
+    if (from_indexer && wave == 0) {
+        const int32_t* g = p.gstats + row * (int64_t)K;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) gw[c] = g[c];
+    }
+    if (tid < NW) sm.seg_off[tid] = tid * W::kCapW;
+    if (GUESS) {
+        // The flag the streaming waves poll for T_spec, cleared while the
+        // loads above are in flight.
+        if (tid == 0) sm.guess_ready = 0;
+        lds_barrier();
+    }
+    const int n = min(max(len, 0), hd.ld);
+    const int cap = hd.capacity;
+    const float* x = hd.scores + row * (int64_t)hd.ld;
     int32_t* out = p.out + row * (int64_t)K;
-    gvr_row_stats* st = p.stats ? p.stats + row : nullptr;
+    gvr_row_stats* st = timed ? p.stats + row : nullptr;
 
     // (a1) row classify: n <= K -> 0..n-1 then -1 padding (part 0 writes).
     if (n <= K) {
@@ -993,7 +1013,7 @@ DEV void topk_body(const Params& p) {
     // This part's slabs [ps0, ps1); waves 1..15 stream them in the
     // speculative pass, wave 0 computes the guess meanwhile and streams
     // nothing: this wave's float4 blocks [sqb, sqe).
-    const int ps = (nslab_row + S - 1) / S;
+    const int ps = div_parts(nslab_row + S - 1, S, hd.s_magic);
     const int ps0 = min(part * ps, nslab_row), ps1 = min(ps0 + ps, nslab_row);
     const int ws = (ps1 - ps0 + W::kSW - 1) / W::kSW;
     const int sw = wave - 1;
@@ -1005,10 +1025,10 @@ DEV void topk_body(const Params& p) {
     // no guess, or the row is at most 2K long: there a guess cuts few
     // candidates and often leaves f(T_spec) < K (a guess also cuts the
     // candidates of longer short rows).
-    const bool all_mode = (!(GUESS && p.prev) || n <= 2 * K) && (n <= cap) && (ws * 256 <= W::kCapW);
-    bool have_prev = GUESS && p.prev && !all_mode;
+    const bool all_mode = (!(GUESS && hd.prev) || n <= 2 * K) && (n <= cap) && (ws * 256 <= W::kCapW);
+    bool have_prev = GUESS && hd.prev && !all_mode;
     // The paper's Phase 2 schedule (secant counting passes), when asked for.
-    const bool secant = GUESS && p.secant && have_prev;
+    const bool secant = GUESS && ((hd.geo >> kGeoSecant) & 1u) && have_prev;
     const bool spec = (all_mode || have_prev) && !secant;
     int gvalid = 0;
     uint32_t gmax = 0u, tspec = 0xFFFFFFFFu;
@@ -1044,13 +1064,8 @@ DEV void topk_body(const Params& p) {
         *same_xcd = sm.scal[2] != 0;
         return sm.scal[3] == S - 1;
     };
-    if (tid < NW) sm.seg_off[tid] = tid * W::kCapW;
 
     if (spec) {
-        if (!all_mode) {
-            if (tid == 0) sm.guess_ready = 0;
-            lds_barrier();
-        }
         // The part's first slabs, by buffer loads over the row's float4
         // blocks (lane offset clamped to the last block; refills past the
         // wave's share re-read its last slab, just fetched). Issuing them can
@@ -1079,14 +1094,14 @@ DEV void topk_body(const Params& p) {
                 // gathered key of rank ceil(65 * m / 2048) from the bottom.
                 // From the indexer, when it scored the sample (one load).
                 GuessStats gs;
-                if (p.gstats) {
+                if (from_indexer) {
                     gs = GuessStats{(uint32_t)gw[0], gw[1], (uint32_t)gw[2], (uint32_t)gw[3], __int_as_float(gw[4])};
                 } else {
                     bool ok[4];
                     float gv[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        ok[c] = pq[c] >= 0 && pq[c] < n;
+                        ok[c] = lane + 64 * c < m_g && pq[c] >= 0 && pq[c] < n;
                         gv[c] = ok[c] ? x[pq[c]] : 0.f;
                     }
                     // (above the refine's first level, which stays free)
@@ -1792,7 +1807,7 @@ DEV void topk_body(const Params& p) {
     if (secant) {
         if (tid < NW) sm.seg_off[tid] = 0;
         // Phase 1: all K guessed scores, 2 per thread.
-        const int32_t* pv = p.prev + row * (int64_t)K;
+        const int32_t* pv = hd.prev + row * (int64_t)K;
         uint32_t mn = 0xFFFFFFFFu, mx = 0u;
         float sum = 0.f;
         int cnt = 0;
@@ -2345,10 +2360,21 @@ DEV void topk_body(const Params& p) {
     }
 }
 
+// Head's fields as scalars (only scalar arguments are preloaded).
 template <int NW, bool NT>
-__global__ __launch_bounds__(Shape<NW>::kBlock) void gvr_topk_kernel(Params p) { topk_body<true, NW, NT>(p); }
+__global__ __launch_bounds__(Shape<NW>::kBlock) void gvr_topk_kernel(const float* scores, const int32_t* row_len,
+                                                                     const int32_t* prev, int32_t ld, int32_t K,
+                                                                     int32_t rows, int32_t chunk, uint32_t s_magic,
+                                                                     int32_t capacity, uint32_t geo, Params p) {
+    topk_body<true, NW, NT>(Head{scores, row_len, prev, ld, K, rows, chunk, s_magic, capacity, geo}, p);
+}
 template <int NW>
-__global__ __launch_bounds__(Shape<NW>::kBlock) void radix_topk_kernel(Params p) { topk_body<false, NW, false>(p); }
+__global__ __launch_bounds__(Shape<NW>::kBlock) void radix_topk_kernel(const float* scores, const int32_t* row_len,
+                                                                       const int32_t* prev, int32_t ld, int32_t K,
+                                                                       int32_t rows, int32_t chunk, uint32_t s_magic,
+                                                                       int32_t capacity, uint32_t geo, Params p) {
+    topk_body<false, NW, false>(Head{scores, row_len, prev, ld, K, rows, chunk, s_magic, capacity, geo}, p);
+}
 
 // ------------------------------------------------------------------ host side
 
@@ -2460,20 +2486,22 @@ gvr_status run(const float* scores, int64_t B, int64_t ld, const int32_t* row_le
     for (int64_t r0 = 0; r0 < B; r0 += kRowsPerLaunch) {
         const int64_t rows = std::min<int64_t>(B - r0, kRowsPerLaunch);
         const int64_t rows_pad = (rows + kXcds - 1) / kXcds * kXcds;
+        Head h;
+        h.scores = scores + r0 * ld;
+        h.row_len = row_len ? row_len + r0 : nullptr;
+        h.prev = guess ? prev + r0 * K : nullptr;
+        h.ld = (int32_t)ld;
+        h.K = K;
+        h.rows = (int32_t)rows;
+        h.chunk = (int32_t)(rows_pad / kXcds * parts);
+        h.capacity = plan.capacity;
+        h.s_magic = (uint32_t)(((1ull << 32) + (uint64_t)parts - 1) / (uint64_t)parts);
+        h.geo = (uint32_t)parts | (uint32_t)o.scatter << kGeoScatter | (uint32_t)guess_stride(K) << kGeoStride |
+                (uint32_t)guess_count(K) << kGeoSamples | (uint32_t)(guess && gstats ? 1 : 0) << kGeoFromIndexer |
+                (uint32_t)(stats ? 1 : 0) << kGeoTimed | (uint32_t)(o.secant ? 1 : 0) << kGeoSecant;
         Params q;
-        q.scores = scores + r0 * ld;
-        q.ld = ld;
-        q.row_len = row_len ? row_len + r0 : nullptr;
-        q.prev = guess ? prev + r0 * K : nullptr;
         q.out = out + r0 * K;
         q.stats = stats ? stats + r0 : nullptr;
-        q.K = K;
-        q.capacity = plan.capacity;
-        q.rows = (int32_t)rows;
-        q.parts = parts;
-        q.chunk = (int32_t)(rows_pad / kXcds * parts);
-        q.scatter = o.scatter;
-        q.secant = o.secant;
         q.paper_refine = o.paper_refine;
         q.arrivals = ws.arrivals;
         q.part_count = ws.part_count;
@@ -2484,27 +2512,21 @@ gvr_status run(const float* scores, int64_t B, int64_t ld, const int32_t* row_le
         q.ordered_merge = o.ordered_merge;
         const dim3 grid((unsigned)(rows_pad * parts));
         const hipStream_t hs = (hipStream_t)stream;
-        if (plan.shape == kNWMid) {
-            const dim3 block(Shape<kNWMid>::kBlock);
-            if (guess)
-                hipLaunchKernelGGL((gvr_topk_kernel<kNWMid, false>), grid, block, 0, hs, q);
-            else
-                hipLaunchKernelGGL(radix_topk_kernel<kNWMid>, grid, block, 0, hs, q);
-        } else if (plan.shape == kNWShort) {
-            const dim3 block(Shape<kNWShort>::kBlock);
-            if (guess)
-                hipLaunchKernelGGL((gvr_topk_kernel<kNWShort, false>), grid, block, 0, hs, q);
-            else
-                hipLaunchKernelGGL(radix_topk_kernel<kNWShort>, grid, block, 0, hs, q);
-        } else {
-            const dim3 block(Shape<kNWLong>::kBlock);
-            if (guess && plan.stream_hint)
-                hipLaunchKernelGGL((gvr_topk_kernel<kNWLong, true>), grid, block, 0, hs, q);
-            else if (guess)
-                hipLaunchKernelGGL((gvr_topk_kernel<kNWLong, false>), grid, block, 0, hs, q);
-            else
-                hipLaunchKernelGGL(radix_topk_kernel<kNWLong>, grid, block, 0, hs, q);
-        }
+        const dim3 block((unsigned)(plan.shape * kWave));
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, hs, h.scores, h.row_len, h.prev, h.ld, h.K, h.rows, h.chunk,
+                               h.s_magic, h.capacity, h.geo, q);
+        };
+        if (plan.shape == kNWMid)
+            guess ? launch(gvr_topk_kernel<kNWMid, false>) : launch(radix_topk_kernel<kNWMid>);
+        else if (plan.shape == kNWShort)
+            guess ? launch(gvr_topk_kernel<kNWShort, false>) : launch(radix_topk_kernel<kNWShort>);
+        else if (!guess)
+            launch(radix_topk_kernel<kNWLong>);
+        else if (plan.stream_hint)
+            launch(gvr_topk_kernel<kNWLong, true>);
+        else
+            launch(gvr_topk_kernel<kNWLong, false>);
         if (hipGetLastError() != hipSuccess) return GVR_ERR_HIP;
     }
     return GVR_OK;
