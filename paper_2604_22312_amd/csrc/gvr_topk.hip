@@ -120,7 +120,6 @@ static_assert(kPartCap == Shape<kNWLong>::kCap, "a workspace slot holds one part
 constexpr int kRefBins = 4096;                 // bins of a narrowing refine level (12 bits of key)
 constexpr int kRefBins1 = 2048;                // bins of the first refine level (32 per lane of one wave)
 constexpr int kDigitShift = 21;                // radix digit: the top 11 key bits, one first-level bin each
-static_assert(kRefBins1 + kGuessBins <= kRefBins, "guess histogram above the first refine level");
 static_assert(kGuessMaxK == GVR_MAX_K, "the T_spec quantile is taken over the largest K");
 static_assert(kRefBins1 == gvr_host::kSlotHistBins, "a workspace slot holds one part's first refine level");
 constexpr int kSmall = 64;                     // refine: K-th key's bin resolved by one wave up to this size
@@ -260,7 +259,7 @@ struct Smem {
     int red[4][NW];
     float redf[NW];
     int scal[8];
-    int guess_ready;                    // set by wave 0 once T_spec is in scal[4..7]
+    uint64_t guess;                     // T_spec | pmax << 32 once wave 0 has them (T_spec >= 1), 0 before
 };
 // Passes over the lists read four 64-entry chunks at a time, up to 255
 // entries past a segment's count (masked afterwards): the list must be
@@ -972,9 +971,9 @@ DEV void topk_body(const Head& hd, const Params& p) {
     }
     if (tid < NW) sm.seg_off[tid] = tid * W::kCapW;
     if (GUESS) {
-        // The flag the streaming waves poll for T_spec, cleared while the
+        // The word the streaming waves poll for T_spec, cleared while the
         // loads above are in flight.
-        if (tid == 0) sm.guess_ready = 0;
+        if (tid == 0) sm.guess = 0;
         lds_barrier();
     }
     const int n = min(max(len, 0), hd.ld);
@@ -1093,36 +1092,29 @@ DEV void topk_body(const Head& hd, const Params& p) {
                 // edge of the histogram bin (over [pmin, pmax]) holding the
                 // gathered key of rank ceil(65 * m / 2048) from the bottom.
                 // From the indexer, when it scored the sample (one load).
-                GuessStats gs;
-                if (from_indexer) {
-                    gs = GuessStats{(uint32_t)gw[0], gw[1], (uint32_t)gw[2], (uint32_t)gw[3], __int_as_float(gw[4])};
-                } else {
-                    bool ok[4];
-                    float gv[4];
+                bool ok[4];
+                float gv[4];
+                if (!from_indexer) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         ok[c] = lane + 64 * c < m_g && pq[c] >= 0 && pq[c] < n;
-                        gv[c] = ok[c] ? x[pq[c]] : 0.f;
+                        gv[c] = x[ok[c] ? pq[c] : 0];   // (n > K >= 1: element 0 exists)
                     }
-                    // (above the refine's first level, which stays free)
-                    gs = guess_from_samples(gv, ok, sm.u.rhist + kRefBins1);
                 }
-                const uint32_t ts = gs.ts, mn = gs.mn, mx = gs.mx;
-                const int cnt = gs.cnt;
-                const float sum = gs.sum;
-                {   // the refine's first level, filled after the pass
+                {   // the refine's first level, filled after the pass; cleared while the gather is in flight
                     int4* r4 = reinterpret_cast<int4*>(sm.u.rhist) + lane * (kRefBins1 / 4 / kWave);
 #pragma unroll
                     for (int j = 0; j < kRefBins1 / 4 / kWave; ++j) r4[j] = make_int4(0, 0, 0, 0);
                 }
+                const GuessStats gs =
+                    from_indexer ? GuessStats{(uint32_t)gw[0], gw[1], (uint32_t)gw[2], (uint32_t)gw[3], __int_as_float(gw[4])}
+                                 : guess_from_samples(gv, ok, timed);
                 if (lane == 0) {
-                    sm.scal[4] = (int)ts;
-                    sm.scal[5] = cnt;
-                    sm.scal[6] = (int)mn;
-                    sm.scal[7] = (int)mx;
-                    sm.redf[0] = sum;
+                    sm.scal[4] = gs.cnt;
+                    sm.redf[0] = gs.sum;
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                    __hip_atomic_store(&sm.guess_ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __hip_atomic_store(&sm.guess, (uint64_t)max(gs.ts, 1u) | (uint64_t)gs.mx << 32, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             }
         }
@@ -1147,14 +1139,12 @@ DEV void topk_body(const Head& hd, const Params& p) {
         // flight (polling an LDS flag, not a barrier: issuing those loads may
         // stall a wave, which must not hold up wave 0).
         if (!all_mode) {
-            while (__hip_atomic_load(&sm.guess_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
+            uint64_t gword;
+            while ((gword = __hip_atomic_load(&sm.guess, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0)
                 __builtin_amdgcn_s_sleep(1);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            tspec = (uint32_t)sm.scal[4];
-            gvalid = sm.scal[5];
-            gmax = (uint32_t)sm.scal[7];
-            gsum = sm.redf[0];
-            if (gvalid == 0) have_prev = false;   // no usable guess: the pass keeps (almost) nothing
+            tspec = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)gword);
+            gmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)(gword >> 32));
         }
         t1 = tstamp();
         tspec = max(tspec, 1u);
@@ -1259,6 +1249,11 @@ DEV void topk_body(const Head& hd, const Params& p) {
         passes = 1;
         lds_barrier();
         t2 = tstamp();   // every wave of the part has streamed its slabs
+        if (!all_mode) {
+            gvalid = sm.scal[4];
+            gsum = sm.redf[0];
+            if (gvalid == 0) have_prev = false;   // no usable guess: the pass kept (almost) nothing
+        }
         overflow = wave_max_u(lane < NW ? (uint32_t)sm.wa[lane] : 0u) > (uint32_t)W::kCapW;
         f_spec = overflow ? -1 : sum_over_waves<NW>(sm.wa, lane);
         hist_ready = own_hist && !overflow;

@@ -117,7 +117,6 @@ __device__ void sample_guess(const IdxParams& p, int b, float* wl) {
     constexpr int MT = H / 16;
     __shared__ float sc[kGuessSamples];
     __shared__ int sv[kGuessSamples];
-    __shared__ int gh[kGuessBins];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = b / p.group;
@@ -172,7 +171,7 @@ __device__ void sample_guess(const IdxParams& p, int b, float* wl) {
             gok[c] = sv[lane + 64 * c] != 0;
             gv[c] = gok[c] ? sc[lane + 64 * c] : 0.f;
         }
-        const GuessStats gs = guess_from_samples(gv, gok, gh);
+        const GuessStats gs = guess_from_samples(gv, gok, true);
         if (lane == 0) {
             int32_t* o = p.gstats + (int64_t)b * p.K;
             o[0] = (int32_t)gs.ts;
