@@ -119,16 +119,18 @@ static_assert(Shape<kNWLong>::kCap == GVR_MAX_CANDIDATES, "the long-row shape ho
 static_assert(kPartCap == Shape<kNWLong>::kCap, "a workspace slot holds one part's lists");
 constexpr int kRefBins = 4096;                 // bins of a narrowing refine level (12 bits of key)
 constexpr int kRefBins1 = 2048;                // bins of the first refine level (32 per lane of one wave)
+constexpr int kCoarse = kRefBins1 / 32;        // coarse bins of that level: one per lane
 constexpr int kDigitShift = 21;                // radix digit: the top 11 key bits, one first-level bin each
 static_assert(kGuessMaxK == GVR_MAX_K, "the T_spec quantile is taken over the largest K");
 static_assert(kRefBins1 == gvr_host::kSlotHistBins, "a workspace slot holds one part's first refine level");
-constexpr int kSmall = 64;                     // refine: K-th key's bin resolved by one wave up to this size
+constexpr int kSmall = 64;                     // refine: K-th key's bin resolved by ranking up to this size
 constexpr int kMaxPasses = 8;                  // 2 + at most 4 narrowing passes + 1 final pass suffice
 constexpr int kMaxSecant = 8;                  // probes of the secant search after T0 (I_max)
 
 static_assert((kBins & (kBins - 1)) == 0 && (kRefBins & (kRefBins - 1)) == 0 && (kRefBins1 & (kRefBins1 - 1)) == 0 &&
                   (kGuessBins & (kGuessBins - 1)) == 0, "bin counts are powers of two");
-static_assert(kSmall * 4 <= kRefBins, "refine candidates over the histogram");
+static_assert(kCoarse == kWave, "one coarse bin per lane");
+static_assert(kRefBins1 + kSmall * 5 <= kRefBins, "refine candidates above the first refine level");
 
 // What a workgroup needs before its first loads, as scalar kernel arguments:
 // the command processor preloads them into SGPRs (the build asks for 14
@@ -259,6 +261,8 @@ struct Smem {
     int red[4][NW];
     float redf[NW];
     int scal[8];
+    int4 hit;                           // bin_search's result (16 waves)
+    int coarse[kCoarse];                // sums of 32 bins each of a first refine level
     uint64_t guess;                     // T_spec | pmax << 32 once wave 0 has them (T_spec >= 1), 0 before
 };
 // Passes over the lists read four 64-entry chunks at a time, up to 255
@@ -481,21 +485,16 @@ DEV uint32_t refine_kth(Smem<NW>& sm, uint32_t wlo, uint32_t whi, int above, int
     return wlo;
 }
 
-// Emission of segment j: the segments before it hold `gb` keys > T and `eb`
-// keys == T; write every key > T and the first `take` keys == T (list order =
-// index order) at their ranks: ascending index output.
-template <int NW>
-DEV void emit_segment(const Smem<NW>& sm, int j, uint32_t T, int K, int take, int gb, int eb, int32_t* out,
-                      int lane) {
-    const uint2* seg = sm.list + sm.seg_off[j];
-    const int cnt = sm.seg_cnt[j];
-    for (int i0 = 0; i0 < cnt; i0 += 4 * kWave) {
-        const int rem = cnt - i0;
-        uint2 en[4];   // four entries per lane read before any is written out
-#pragma unroll
-        for (int c = 0; c < 4; ++c) en[c] = seg[i0 + c * kWave + lane];   // past the count: masked below
+// Emission of one segment (cnt entries at seg, the first four per lane in
+// `first`): the segments before it hold `gb` keys > T and `eb` keys == T;
+// write every key > T and the first `take` keys == T (list order = index
+// order) at their ranks: ascending index output.
+DEV void emit_segment(const uint2* seg, int cnt, const uint2 (&first)[4], uint32_t T, int K, int take, int gb, int eb,
+                      int32_t* out, int lane) {
+    auto emit4 = [&](const uint2 (&en)[4], int rem) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
+            if (rem <= c * kWave) break;   // (wave-uniform)
             const uint64_t vm = first_lanes(rem - c * kWave);   // valid lanes
             const uint32_t kk = en[c].x;
             const uint64_t mg = __ballot(kk > T) & vm, me = __ballot(kk == T) & vm;
@@ -515,15 +514,13 @@ DEV void emit_segment(const Smem<NW>& sm, int j, uint32_t T, int K, int take, in
             gb += __popcll(mg);
             eb += __popcll(me);
         }
-    }
-}
-
-// Every wave emits its segments at the offsets in sga / sgb (after seg_scan).
-template <int NW>
-DEV void emit_segments(const Smem<NW>& sm, uint32_t T, int K, int take, int32_t* out, int lane, int wave) {
-    {
-        const int j = wave;
-        emit_segment(sm, j, T, K, take, sm.sga[j], sm.sgb[j], out, lane);
+    };
+    emit4(first, cnt);
+    for (int i0 = 4 * kWave; i0 < cnt; i0 += 4 * kWave) {
+        uint2 en[4];   // four entries per lane read before any is written out
+#pragma unroll
+        for (int c = 0; c < 4; ++c) en[c] = seg[i0 + c * kWave + lane];   // past the count: masked
+        emit4(en, cnt - i0);
     }
 }
 
@@ -553,7 +550,11 @@ DEV void emit_from_lists(Smem<NW>& sm, uint32_t T, int K, int32_t* out, int tid,
     if (wave == 0) seg_scan(sm, NW, lane);
     lds_barrier();
     const int gtot = sm.scal[5];
-    emit_segments(sm, T, K, K - gtot, out, lane, wave);
+    const uint2* seg = sm.list + sm.seg_off[wave];
+    uint2 first[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) first[c] = seg[c * kWave + lane];   // past the count: masked
+    emit_segment(seg, sm.seg_cnt[wave], first, T, K, K - gtot, sm.sga[wave], sm.sgb[wave], out, lane);
     *n_gt_out = gtot;
 }
 
@@ -727,73 +728,112 @@ DEV void keys_in_place(Smem<NW>& sm, uint2* seg, int cnt, bool hist, uint32_t rl
     }
 }
 
-// Wave 0: the bin b of a first refine level hb[0, kRefBins1) holding the
-// need0-th key from the top (need0 >= 1, at most the histogram's total), with
-// two wave scans; scal[0] = b, scal[2] = base + the keys in the bins above b,
-// scal[3] = b's count.
-template <int NW>
-DEV void kth_bin_wave0(Smem<NW>& sm, const int* hb, int need0, int base, int lane) {
-    // lane l owns bins [32 l, 32 l + 32)
-    const int4* h4 = reinterpret_cast<const int4*>(hb) + lane * 8;
-    int s = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int4 v = h4[j];
-        s += v.x + v.y + v.z + v.w;
-    }
+// The bin b of a first refine level hb[0, kRefBins1) holding the need0-th key
+// from the top (need0 >= 1): `above` = base + the keys in the bins above b,
+// `cnt` = b's count, `total` = the level's keys. With total < need0 there is
+// no such bin and b = 0.
+struct BinHit {
+    int b, above, cnt, total;
+};
+// From the 64 sums s of 32 bins each, one per lane.
+DEV BinHit bin_from_sums(const int* hb, int s, int need0, int base, int lane) {
     const int incl = wave_incl_scan(s, lane);
     const int total = __builtin_amdgcn_readlane(incl, 63);
     const int abv = total - incl;   // keys in the bins of higher lanes
     const uint64_t hit = __ballot(abv < need0 && abv + s >= need0);
     const int L = hit ? (int)__builtin_ctzll(hit) : 0;
     const int abv_l = __builtin_amdgcn_readlane(abv, L);
+    const int s_l = __builtin_amdgcn_readlane(s, L);
     const int hj = lane < 32 ? hb[L * 32 + lane] : 0;
-    const int ij = wave_incl_scan(hj, lane);
-    const int s_l = __builtin_amdgcn_readlane(ij, 63);
-    const int abj = abv_l + s_l - ij;
+    const int abj = abv_l + s_l - wave_incl_scan(hj, lane);
     const uint64_t hit2 = __ballot(lane < 32 && abj < need0 && abj + hj >= need0);
     const int J = hit2 ? (int)__builtin_ctzll(hit2) : 0;
-    if (lane == 0) {
-        sm.scal[0] = L * 32 + J;
-        sm.scal[2] = base + __builtin_amdgcn_readlane(abj, J);
-        sm.scal[3] = __builtin_amdgcn_readlane(hj, J);
+    return BinHit{L * 32 + J, base + __builtin_amdgcn_readlane(abj, J), __builtin_amdgcn_readlane(hj, J), total};
+}
+// All threads; the level is complete behind the caller's last barrier. Every
+// wave sums its share of the bins into coarse ones (consecutive bins per
+// lane, free of bank conflicts, and lane moves inside a DPP row; one wave
+// reading 32 bins per lane conflicts on every read and took 0.5 us more).
+// Behind a barrier, 16 waves: wave 0 finds the bin and hands it over, alone
+// on its SIMD (sixteen waves repeating the search take 0.2 us longer on one
+// 8K row); 8 and 4 waves: every wave finds it for itself (2048 rows of 8K
+// 47.9 -> 46.7 us). Leaves scal[1] at 0 for the refine.
+template <int NW>
+DEV BinHit bin_search(Smem<NW>& sm, const int* hb, int need0, int base, int tid) {
+    const int lane = tid & 63;
+    constexpr int PER = kRefBins1 / Shape<NW>::kBlock;   // bins per thread: 2, 4 or 8
+    int s = 0;
+    if constexpr (PER == 2) {
+        const int2 v = reinterpret_cast<const int2*>(hb)[tid];
+        s = v.x + v.y;
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER / 4; ++j) {
+            const int4 v = reinterpret_cast<const int4*>(hb)[tid * (PER / 4) + j];
+            s += v.x + v.y + v.z + v.w;
+        }
+    }
+    s += dpp_i<kQuadSwap1>(0, s);
+    s += dpp_i<kQuadSwap2>(0, s);
+    if (PER <= 4) s += dpp_i<kRowHalfMirror>(0, s);
+    if (PER <= 2) s += dpp_i<kRowMirror>(0, s);
+    if ((tid & (32 / PER - 1)) == 0) sm.coarse[tid * PER / 32] = s;
+    if (tid == 0) sm.scal[1] = 0;
+    lds_barrier();
+    if constexpr (NW == kNWLong) {
+        if ((tid >> 6) == 0) {
+            const BinHit r = bin_from_sums(hb, sm.coarse[lane], need0, base, lane);
+            if (lane == 0) sm.hit = make_int4(r.b, r.above, r.cnt, r.total);
+        }
+        lds_barrier();
+        const int4 h = sm.hit;
+        return BinHit{__builtin_amdgcn_readfirstlane(h.x), __builtin_amdgcn_readfirstlane(h.y),
+                      __builtin_amdgcn_readfirstlane(h.z), __builtin_amdgcn_readfirstlane(h.w)};
+    } else {
+        return bin_from_sums(hb, sm.coarse[lane], need0, base, lane);
     }
 }
 
 // Exact K-th key T* among the listed candidates and the emission. The K-th
 // key lies in [rlo, rhi]; `above` listed keys lie above rhi. One histogram
 // level of kRefBins1 bins over [rlo, bin_hi] (keys in (bin_hi, rhi] count in
-// the top bin; built here unless `hist_ready`), then wave 0 finds the
-// bin b holding the K-th key with two wave scans. If b holds at most kSmall
+// the top bin; built and searched here unless `ready` holds the search's
+// result) gives the bin b holding the K-th key. If b holds at most kSmall
 // candidates, one pass over the lists copies them (with their segment) to a
-// small LDS array and counts each segment's keys above b; wave 0 takes one
-// candidate per lane, selects T* among them and the per-segment emission
-// offsets, and every wave emits its segments. Otherwise histogram narrowing
-// (refine_kth) continues inside b; a bin whose keys are all one value (ties)
-// is resolved by its first level.
+// small LDS array and counts each segment's keys above b; the rank of each
+// among them gives T* and the segments' emission offsets, and every wave
+// emits its segment. Otherwise histogram narrowing (refine_kth) continues
+// inside b; a bin whose keys are all one value (ties) is resolved by its
+// first level. The time is the latency of these steps, not their work.
 template <int NW>
 DEV uint32_t refine_emit(Smem<NW>& sm, uint32_t rlo, uint32_t rhi, uint32_t bin_hi, int above, int K, int32_t* out,
-                         int tid, int* n_gt_out, bool hist_ready) {
+                         int tid, int* n_gt_out, const BinHit* ready) {
     using W = Shape<NW>;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t sh = ref_shift(rlo, bin_hi);
     int* hb = sm.u.rhist;
-    if (tid == 0) sm.scal[1] = 0;   // ordered before its atomics by the barrier after the bin search
-    if (!hist_ready) {
+    BinHit bh;
+    if (ready) {
+        bh = *ready;
+    } else {
         for (int i = tid; i < kRefBins1; i += W::kBlock) hb[i] = 0;
         lds_barrier();
         for_my_keys(sm, wave, lane, [&](uint32_t kk) {
             if (kk >= rlo && kk <= rhi) ref_hist_add(sm, kk, rlo, sh);
         });
         lds_barrier();
+        bh = bin_search(sm, hb, K - above, above, tid);   // K - above >= 1: T*'s rank in [rlo, rhi], from the top
     }
-    // (a ready histogram is complete behind the caller's last barrier)
-    const int need0 = K - above;   // >= 1: rank of T* among the keys in [rlo, rhi], from the top
-    if (wave == 0) kth_bin_wave0(sm, hb, need0, above, lane);
-    lds_barrier();
-    const int b = sm.scal[0];
-    const int above_b = sm.scal[2];   // listed keys above bin b
-    const int cnt_b = sm.scal[3];
+    // This wave's segment: its first four entries per lane stay in registers
+    // for the copy and the emission (most segments hold no more).
+    const uint2* const seg = sm.list + sm.seg_off[wave];
+    const int cnt = sm.seg_cnt[wave];
+    uint2 first[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) first[c] = seg[c * kWave + lane];   // past the count: masked below
+    const int b = bh.b;
+    const int above_b = bh.above;   // listed keys above bin b
+    const int cnt_b = bh.cnt;
     const uint64_t lo64 = (uint64_t)rlo + ((uint64_t)b << sh);
     const uint32_t lo_b = (uint32_t)lo64;
     const uint32_t hi_b =
@@ -808,64 +848,65 @@ DEV uint32_t refine_emit(Smem<NW>& sm, uint32_t rlo, uint32_t rhi, uint32_t bin_
         emit_from_lists(sm, kth, K, out, tid, n_gt_out);
         return kth;
     }
-    // Copy bin b's candidates, with their segment, to one small LDS array over
-    // the histogram (no longer needed; at most kSmall of them): a chunk that
-    // holds some (rare) reserves room with one LDS atomic. Each wave counts
-    // its segments' keys above the bin.
-    uint4* const small = reinterpret_cast<uint4*>(sm.u.rhist);
+    // Copy bin b's candidates, with their segment, to one small LDS array
+    // above the histogram's bins (other waves may still read those): a chunk
+    // that holds some (rare) reserves room with one LDS atomic. Each wave
+    // counts its segment's keys above the bin.
+    uint4* const small = reinterpret_cast<uint4*>(sm.u.rhist + kRefBins1);
     uint32_t* const skey = reinterpret_cast<uint32_t*>(small + kSmall);   // their keys alone, for the rank
     const uint32_t wid = hi_b - lo_b;
-    {
-        const int j = wave;
-        const uint2* seg = sm.list + sm.seg_off[j];
-        const int cnt = sm.seg_cnt[j];
-        int gtl = 0;
-        for (int i0 = 0; i0 < cnt; i0 += 4 * kWave) {
-            uint2 en[4];
+    int gtl = 0;
+    auto copy4 = [&](const uint2 (&en)[4], int i0) {
+        // per lane: keys above the bin counted, bin members flagged (one
+        // ballot for the four entries: members are rare)
+        bool hit[4] = {false, false, false, false};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) en[c] = seg[i0 + c * kWave + lane];   // past the count: masked below
-            // per lane: keys above the bin counted, bin members flagged (one
-            // ballot for the four entries: members are rare)
-            bool hit[4];
+        for (int c = 0; c < 4; ++c) {
+            if (i0 + c * kWave >= cnt) break;   // (wave-uniform)
+            const bool valid = i0 + c * kWave + lane < cnt;
+            gtl += (valid && en[c].x > hi_b) ? 1 : 0;
+            hit[c] = valid && en[c].x - lo_b <= wid;
+        }
+        if (!__ballot(hit[0] || hit[1] || hit[2] || hit[3])) return;   // (wave-uniform)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const bool valid = i0 + c * kWave + lane < cnt;
-                gtl += (valid && en[c].x > hi_b) ? 1 : 0;
-                hit[c] = valid && en[c].x - lo_b <= wid;
-            }
-            if (!__ballot(hit[0] || hit[1] || hit[2] || hit[3])) continue;   // (wave-uniform)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint64_t m = __ballot(hit[c]);
-                if (m) {   // (wave-uniform)
-                    int base = 0;
-                    if (lane == 0)
-                        base = __hip_atomic_fetch_add(&sm.scal[1], (int)__popcll(m), __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_WORKGROUP);
-                    base = __builtin_amdgcn_readfirstlane(base);
-                    const int pos = base + (int)lanes_below(m, 0);
-                    if (((m >> lane) & 1) && pos < kSmall) {
-                        small[pos] = make_uint4(en[c].x, en[c].y, (uint32_t)j, 0u);
-                        skey[pos] = en[c].x;
-                    }
+        for (int c = 0; c < 4; ++c) {
+            const uint64_t m = __ballot(hit[c]);
+            if (m) {   // (wave-uniform)
+                int base = 0;
+                if (lane == 0)
+                    base = __hip_atomic_fetch_add(&sm.scal[1], (int)__popcll(m), __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+                base = __builtin_amdgcn_readfirstlane(base);
+                const int pos = base + (int)lanes_below(m, 0);
+                if (((m >> lane) & 1) && pos < kSmall) {
+                    small[pos] = make_uint4(en[c].x, en[c].y, (uint32_t)wave, 0u);
+                    skey[pos] = en[c].x;
                 }
             }
         }
-        const int gt_hi = wave_sum(gtl);
-        if (lane == 0) {
-            sm.sga[j] = gt_hi;
-            sm.sgb[j] = 0;
-        }
+    };
+    copy4(first, 0);
+    for (int i0 = 4 * kWave; i0 < cnt; i0 += 4 * kWave) {
+        uint2 en[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) en[c] = seg[i0 + c * kWave + lane];   // past the count: masked
+        copy4(en, i0);
+    }
+    gtl = wave_sum(gtl);
+    if (lane == 0) {
+        sm.sga[wave] = gtl;
+        sm.sgb[wave] = 0;
     }
     lds_barrier();
-    if (wave == 0) {
-        // Lane l takes the l-th copied candidate (any order).
-        const bool v = lane < cnt_b;
-        const uint4 mine = v ? small[lane] : make_uint4(0u, 0u, 0u, 0u);
-        // T* is the need-th largest of them: the key of a lane with fewer
-        // than `need` keys above it and at least `need` at or above it. Every
-        // lane compares its key with each candidate's, four keys per LDS
-        // read (one address for the whole wave: a broadcast).
+    // T*: lane l takes the l-th copied candidate (any order); T* is the
+    // need-th largest of them: the key of a lane with fewer than `need` keys
+    // above it and at least `need` at or above it. Every lane compares its
+    // key with each candidate's, four keys per LDS read (one address for the
+    // whole wave: a broadcast).
+    const bool v = lane < cnt_b;
+    uint4 mine;
+    auto rank = [&]() -> uint32_t {
+        mine = small[lane];   // past cnt_b: masked by v
         const int need = K - above_b;   // rank of T* inside the bin, from the top
         const uint4* sk4 = reinterpret_cast<const uint4*>(skey);
         int gt = 0, ge = 0;
@@ -881,18 +922,37 @@ DEV uint32_t refine_emit(Smem<NW>& sm, uint32_t rlo, uint32_t rhi, uint32_t bin_
             }
         }
         const uint64_t hitk = __ballot(v && gt < need && ge >= need);
-        const uint32_t kth = __builtin_amdgcn_readlane(mine.x, hitk ? (int)__builtin_ctzll(hitk) : 0);
-        // Per segment: keys > T* (above the bin, plus the bin's) and == T*;
-        // each candidate adds itself to its segment's counts.
-        if (v && mine.x > kth) __hip_atomic_fetch_add(&sm.sga[mine.z], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (v && mine.x == kth) __hip_atomic_fetch_add(&sm.sgb[mine.z], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        seg_scan(sm, NW, lane);
-        if (lane == 0) sm.scal[0] = (int)kth;
+        return __builtin_amdgcn_readlane(mine.x, hitk ? (int)__builtin_ctzll(hitk) : 0);
+    };
+    uint32_t kth;
+    int gb, eb, gtot;   // keys > T* and == T* in the segments before this wave's; keys > T* in all
+    if constexpr (NW == kNWLong) {
+        // 16 waves: wave 0 alone, as in bin_search. Per segment: keys > T*
+        // (above the bin, plus the bin's) and == T*; each candidate adds
+        // itself to its segment's counts.
+        if (wave == 0) {
+            const uint32_t t = rank();
+            if (v && mine.x > t) __hip_atomic_fetch_add(&sm.sga[mine.z], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (v && mine.x == t) __hip_atomic_fetch_add(&sm.sgb[mine.z], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            seg_scan(sm, NW, lane);
+            if (lane == 0) sm.scal[0] = (int)t;
+        }
+        lds_barrier();
+        kth = (uint32_t)sm.scal[0];
+        gtot = sm.scal[5];
+        gb = sm.sga[wave];
+        eb = sm.sgb[wave];
+    } else {
+        // 8 and 4 waves: every wave ranks, and counts its own offsets.
+        const int seg_gt = lane < wave ? sm.sga[lane] : 0;   // keys above the bin in the segments before
+        kth = rank();
+        const uint64_t bin_gt = __ballot(v && mine.x > kth), bin_eq = __ballot(v && mine.x == kth);
+        const uint64_t before = __ballot(v && (int)mine.z < wave);
+        gb = wave_sum(seg_gt) + (int)__popcll(bin_gt & before);
+        eb = (int)__popcll(bin_eq & before);
+        gtot = above_b + (int)__popcll(bin_gt);
     }
-    lds_barrier();
-    const uint32_t kth = (uint32_t)sm.scal[0];
-    const int gtot = sm.scal[5];
-    emit_segments(sm, kth, K, K - gtot, out, lane, wave);
+    emit_segment(seg, cnt, first, kth, K, K - gtot, gb, eb, out, lane);
     *n_gt_out = gtot;
     return kth;
 }
@@ -1035,7 +1095,8 @@ DEV void topk_body(const Head& hd, const Params& p) {
     int64_t t1 = t0, t2 = t0;
     int passes = 0;
     int f_spec = 0;          // f(tthr), or -1 if unknown
-    bool hist_ready = false; // the refine's first histogram level is built (lists at tthr)
+    bool hist_ready = false; // the refine's first histogram level is built and searched (lists at tthr)
+    BinHit row_hit = {};     // ... the K-th key's bin in it
     bool hist_full = false;  // rhist counts every key >= tthr of the row (first-level bins)
     uint32_t tthr = 0u;      // threshold of the speculative lists
     bool overflow = false;
@@ -1254,8 +1315,17 @@ DEV void topk_body(const Head& hd, const Params& p) {
             gsum = sm.redf[0];
             if (gvalid == 0) have_prev = false;   // no usable guess: the pass kept (almost) nothing
         }
-        overflow = wave_max_u(lane < NW ? (uint32_t)sm.wa[lane] : 0u) > (uint32_t)W::kCapW;
-        f_spec = overflow ? -1 : sum_over_waves<NW>(sm.wa, lane);
+        if (own_hist && S == 1) {
+            // The level counts every key >= T_spec, full lists or not: its
+            // total is f(T_spec), and the K-th key's bin follows from it.
+            const int wc = lane < NW ? sm.wa[lane] : 0;
+            row_hit = bin_search(sm, sm.u.rhist, K, 0, tid);
+            overflow = __ballot(wc > W::kCapW) != 0;
+            f_spec = overflow ? -1 : row_hit.total;
+        } else {
+            overflow = wave_max_u(lane < NW ? (uint32_t)sm.wa[lane] : 0u) > (uint32_t)W::kCapW;
+            f_spec = overflow ? -1 : sum_over_waves<NW>(sm.wa, lane);
+        }
         hist_ready = own_hist && !overflow;
         hist_full = own_hist && S == 1;   // full lists or not, every kept key is in it
         tthr = tspec;
@@ -1521,6 +1591,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
                         sm.seg_cnt[tid] = min(chunk, f_spec - o);
                     }
                                     lds_barrier();   // every wave reads the merged list, its segment table and histogram after this
+                    if (!all_mode) row_hit = bin_search(sm, sm.u.rhist, K, 0, tid);
                 }
             }
             // Ready for the next call (issued after the loads above).
@@ -1537,7 +1608,8 @@ DEV void topk_body(const Head& hd, const Params& p) {
         int snaps = 0;
         const uint32_t kth = p.paper_refine
                                  ? paper_refine_emit(sm, K, out, tid, &ngt, &snaps)
-                                 : refine_emit(sm, tthr, 0xFFFFFFFFu, max(gmax, tthr), 0, K, out, tid, &ngt, hist_ready);
+                                 : refine_emit(sm, tthr, 0xFFFFFFFFu, max(gmax, tthr), 0, K, out, tid, &ngt,
+                                               hist_ready ? &row_hit : nullptr);
         if (st && tid == 0) {
             gvr_row_stats s = {};
             s.n = n;
@@ -1782,7 +1854,6 @@ DEV void topk_body(const Head& hd, const Params& p) {
 
     int path = all_mode ? GVR_PATH_ALL : (have_prev ? GVR_PATH_GUESS : GVR_PATH_NO_GUESS);
     uint32_t T = 0, rlo = 0, rhi = 0xFFFFFFFFu, bin_hi = 0xFFFFFFFFu;
-    bool use_hist = false;   // the refine's first level is already counted
     int above = 0, cands = 0;
     bool done_lists = false;   // lists hold every key >= T
     bool ties = false;
@@ -1982,7 +2053,6 @@ DEV void topk_body(const Head& hd, const Params& p) {
         T = tthr;
         cands = f_spec;
         done_lists = true;
-        use_hist = hist_ready && !all_mode;
         rlo = tthr;
         rhi = 0xFFFFFFFFu;
         bin_hi = max(gmax, tthr);
@@ -2109,10 +2179,8 @@ DEV void topk_body(const Head& hd, const Params& p) {
             above = 0;
         } else if (spec && !secant && f_spec > cap && hist_full) {
             __syncthreads();   // the level is complete
-            if (wave == 0) kth_bin_wave0(sm, sm.u.rhist, K, 0, lane);
-            __syncthreads();
-            const int b = sm.scal[0], above_b = sm.scal[2], cnt_b = sm.scal[3];
-            __syncthreads();
+            const BinHit bh = bin_search(sm, sm.u.rhist, K, 0, tid);
+            const int b = bh.b, above_b = bh.above, cnt_b = bh.cnt;
             const uint32_t hsh = ref_shift(tthr, max(gmax, tthr));
             const uint64_t lo64 = (uint64_t)tthr + ((uint64_t)b << hsh);
             const uint64_t end64 = std::min<uint64_t>(lo64 + ((uint64_t)1 << hsh) - 1, 0xFFFFFFFFu);
@@ -2134,10 +2202,8 @@ DEV void topk_body(const Head& hd, const Params& p) {
             // Nothing bounds the K-th key: a digit pass, then the same choice
             // over its bins (a bin of more than C keys is narrowed).
             if (!digits_counted) digit_pass(qb, qe);
-            if (wave == 0) kth_bin_wave0(sm, sm.u.rhist, K, 0, lane);
-            __syncthreads();
-            const int b = sm.scal[0], above_b = sm.scal[2], cnt_b = sm.scal[3];
-            __syncthreads();
+            const BinHit bh = bin_search(sm, sm.u.rhist, K, 0, tid);
+            const int b = bh.b, above_b = bh.above, cnt_b = bh.cnt;
             const uint32_t lo_b = (uint32_t)b << kDigitShift;
             const uint32_t hi_b = lo_b + ((1u << kDigitShift) - 1u);
             if (above_b + cnt_b <= cap) {
@@ -2331,7 +2397,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
     int ngt = 0;
     int snaps = 0;
     const uint32_t kth = p.paper_refine ? paper_refine_emit(sm, K, out, tid, &ngt, &snaps)
-                                        : refine_emit(sm, rlo, rhi, bin_hi, above, K, out, tid, &ngt, use_hist);
+                                        : refine_emit(sm, rlo, rhi, bin_hi, above, K, out, tid, &ngt, nullptr);
     if (st && tid == 0) {
         gvr_row_stats s = {};
         s.n = n;
