@@ -48,6 +48,8 @@ constexpr int64_t kMaxLd = ((int64_t)1 << 31) - 16;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+constexpr int kBufWord3 = 0x00020000;    // raw buffer resource: 32-bit data format, no swizzle
 constexpr int kUnitScales = 0x7F7F7F7F;  // E8M0 block scales of 1.0 for the scaled matrix op
 
 struct IdxParams {
@@ -79,14 +81,15 @@ __device__ __forceinline__ v8i load32(const uint8_t* p) {
     return v8i{(int)a.x, (int)a.y, (int)a.z, (int)a.w, (int)b.x, (int)b.y, (int)b.z, (int)b.w};
 }
 
-// Score of the key in this lane's column of a 16-key tile for one row:
-// the H / 16 matrix steps (16 heads x 16 keys, the whole head dimension per
-// step), the key's scale, ReLU, the head weights wv (LDS, float4 per lane
-// quarter) and the sum over heads; every lane of the key's column ends with
-// it. The main loop and the fused guess both score keys here, so a sampled
-// key's score equals the one written for it.
+// This lane's quarter of the score of the key in its column of a 16-key tile
+// for one row: the H / 16 matrix steps (16 heads x 16 keys, the whole head
+// dimension per step), the key's scale, ReLU, the head weights wv (LDS,
+// float4 per lane quarter) and the sum over the lane's heads. The score is
+// (q0 + q1) + (q2 + q3) over the column's four lanes, in the main loop
+// (pair_scores) and in the fused guess (column_sum) alike, so a sampled key's
+// score equals the one written for it.
 template <int H>
-__device__ __forceinline__ float tile_score(const v8i (&qa)[H / 16], const v8i& kb, float ks, const float4* wv,
+__device__ __forceinline__ float tile_quarter(const v8i (&qa)[H / 16], const v8i& kb, float ks, const float4* wv,
                                             int quarter) {
     constexpr int MT = H / 16;
     v4f acc[MT];
@@ -103,9 +106,24 @@ __device__ __forceinline__ float tile_score(const v8i (&qa)[H / 16], const v8i& 
         sum += wq.z * fmaxf(acc[mt][2] * ks, 0.f);
         sum += wq.w * fmaxf(acc[mt][3] * ks, 0.f);
     }
-    sum += __shfl_xor(sum, 16, kWave);
-    sum += __shfl_xor(sum, 32, kWave);   // the four lanes of the key now hold its score
     return sum;
+}
+
+// Lane moves of gfx950: rows16 exchanges the odd 16-lane rows of a with the
+// even ones of b, rows32 the upper half of a with the lower half of b; each
+// returns the sum of the two registers afterwards.
+__device__ __forceinline__ float rows16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float rows32(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// The score of this lane's column from its lanes' quarters, in every lane.
+__device__ __forceinline__ float column_sum(float q) {
+    q = rows16(q, q);
+    return rows32(q, q);
 }
 
 // The fused guess of row b = blockIdx.x - sample_base: wave w scores samples
@@ -156,7 +174,7 @@ __device__ void sample_guess(const IdxParams& p, int b, float* wl) {
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        const float v = tile_score<H>(qa, kb[t], ks[t], wv, quarter);
+        const float v = column_sum(tile_quarter<H>(qa, kb[t], ks[t], wv, quarter));
         if (quarter == 0) {
             sc[64 * wave + 16 * t + col] = v;
             sv[64 * wave + 16 * t + col] = ok[t];
@@ -184,7 +202,7 @@ __device__ void sample_guess(const IdxParams& p, int b, float* wl) {
 }
 
 template <int H, int D, int RG>
-__global__ __launch_bounds__(kWaves * kWave) void indexer_kernel(IdxParams p) {
+__global__ __launch_bounds__(kWaves * kWave, 2) void indexer_kernel(IdxParams p) {
     constexpr int MT = H / 16;   // 16-head row tiles
     __shared__ float wl[kWaves][RG * H];
     if (p.prev && (int)blockIdx.x >= p.sample_base) {
@@ -238,40 +256,51 @@ __global__ __launch_bounds__(kWaves * kWave) void indexer_kernel(IdxParams p) {
     __builtin_amdgcn_wave_barrier();   // a wave's LDS accesses complete in order: its reads see its writes
     const float4* wv = reinterpret_cast<const float4*>(&wl[wave][0]);
 
-    const uint8_t* kg = p.k + (int64_t)g * p.ld * D + qoff;
-    const float* sg = p.k_scale + (int64_t)g * p.ld;
-    float* out = p.scores + row0 * p.ld;
-    // Column col of half t of slot u is key min(s_begin + 32 u + 16 t + col,
-    // s_end - 1): lanes past the run recompute the run's last key and store
-    // the same value there, so loads, matrix steps and stores run without
-    // branches and the loads stay in flight across iterations.
-    const int tiles = (int)((s_end - s_begin + kTile - 1) / kTile);
-    auto key_at = [&](int u, int t) { return min(s_begin + (int64_t)u * kTile + 16 * t + col, s_end - 1); };
+    // The run's keys and scales through buffer resources over exactly
+    // [s_begin, s_end): a slot's offset is a scalar and the lane's offset
+    // inside a slot a constant, so a load costs no vector instruction, and
+    // lanes past the run read zeros (their scores are not stored). The slot
+    // offset is clamped to the last slot: the range check subtracts it from
+    // the size.
+    const int run = (int)(s_end - s_begin);
+    const int tiles = (run + kTile - 1) / kTile;
+    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(p.k + ((int64_t)g * p.ld + s_begin) * D), (short)0, run * D, kBufWord3);
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(p.k_scale + (int64_t)g * p.ld + s_begin), (short)0, run * 4, kBufWord3);
+    const int koff = col * D + qoff, soff = col * 4;
     struct Slot {
         v8i kb[2];
         float ks[2];
     };
     auto load_slot = [&](int u) {
+        const int us = min(u, tiles - 1);
         Slot r;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const int64_t key = key_at(u, t);
-            r.kb[t] = load32(kg + key * D);
-            r.ks[t] = sg[key];
+            const v4u a = __builtin_amdgcn_raw_buffer_load_b128(krsrc, koff + 16 * t * D, us * (kTile * D), 0);
+            const v4u b = __builtin_amdgcn_raw_buffer_load_b128(krsrc, koff + 16 * t * D + 16, us * (kTile * D), 0);
+            r.kb[t] = v8i{(int)a.x, (int)a.y, (int)a.z, (int)a.w, (int)b.x, (int)b.y, (int)b.z, (int)b.w};
+            r.ks[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(srsrc, soff + 64 * t, us * (kTile * 4), 0));
         }
         return r;
     };
+    // The lane that stores: the exchanges below leave key 32 u + lane % 32 of
+    // row slot lane / 32 in each lane (one row: in the lower half).
+    const int my_rr = RG == 2 ? lane >> 5 : 0;
+    const int my_n = (int)min((RG == 2 && my_rr ? nr[RG - 1] : nr[0]) - s_begin, (int64_t)run);   // this row's keys of the run
+    float* const my_out = p.scores + (row0 + my_rr) * p.ld + s_begin + (lane & 31);
+    const int my_key = RG == 2 || lane < 32 ? lane & 31 : 1 << 30;
     auto use_slot = [&](const Slot& r, int u) {
+        float c[RG];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int rr = 0; rr < RG; ++rr) {
-                const float sum = tile_score<H>(qa[rr], r.kb[t], r.ks[t], wv + rr * (H / 4), quarter);
-                // the run covers the longer row of the pair: store this row's own keys
-                const int64_t key = key_at(u, t);
-                if (key < nr[rr]) out[rr * p.ld + key] = sum;
-            }
+        for (int rr = 0; rr < RG; ++rr) {
+            const float a = tile_quarter<H>(qa[rr], r.kb[0], r.ks[0], wv + rr * (H / 4), quarter);
+            const float b = tile_quarter<H>(qa[rr], r.kb[1], r.ks[1], wv + rr * (H / 4), quarter);
+            c[rr] = rows16(a, b);   // rows q0 + q1 (even: tile 0, odd: tile 1), upper half q2 + q3
         }
+        const float score = rows32(c[0], c[RG - 1]);
+        if (my_key + u * kTile < my_n) my_out[u * kTile] = score;
     };
     Slot ring[kRing];
 #pragma unroll
