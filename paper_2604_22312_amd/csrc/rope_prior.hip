@@ -1,27 +1,38 @@
 // rope_prior.hip -- the static RoPE/YaRN prior P_static (Sec. 3.2, 3.3) on
 // MI355X (gfx950), behind the C ABI declared in include/gvr_rope_prior.h.
 //
-//   g kernel. One thread per relative position Delta (256-thread
-//   workgroups). The first d/2 threads of every workgroup derive the YaRN
-//   angles theta'_i into LDS (a few pow/log calls, the same in every
-//   workgroup), then each thread sums cos(Delta * theta'_i) over the pairs in
-//   float64 and stores g(Delta). Compute-bound on fp64 cos; run once per
-//   model and length, not per decode step.
+//   g kernel. Four lanes per relative position Delta (1024-thread
+//   workgroups, 256 positions each). The first d/2 threads of every workgroup
+//   derive the YaRN angles theta'_i into LDS (a few pow/log calls, the same
+//   in every workgroup), then each lane sums cos(Delta * theta'_i) over every
+//   fourth pair in float64 and the four sums are added as (0 + 1) + (2 + 3).
+//   Bound by the latency of the float64 cosines: one thread per position left
+//   two waves per SIMD at 131072 positions. Run once per model and length,
+//   not per decode step.
 //
-//   select kernel. One workgroup of 1024 threads finds the K-th largest g by
-//   a radix select over the 64-bit order-preserving key of each float64
-//   (digits of 11, 11, 11, 11, 10, 10 bits; an LDS histogram per digit). The
-//   first digits read g from global memory (L2-resident at these lengths);
-//   as soon as the elements sharing the selected prefix fit in LDS (<= 4096)
-//   they are gathered there and the remaining digits never touch memory
-//   again. A final pass in index order writes every Delta whose key beats
-//   the K-th key, plus the first equal ones, at offsets from two block scans
-//   per 4096-element chunk, so the output comes out in ascending order.
+//   select kernel. One workgroup of 1024 threads, because the calls take no
+//   scratch memory that several could meet in; so it is bound by one compute
+//   unit's read rate and reads g twice. The first pass counts every element
+//   into linear bins over [-d, d] (g cannot leave it), one histogram per wave:
+//   that gives the bin holding the K-th largest g and the place of each
+//   wave's elements at or above it. The second lists the indices of those, in
+//   index order, and the keys of the bin's own elements, which are ranked
+//   among themselves (lower index first); a block scan writes the selected
+//   indices. (A radix select over the 64-bit keys read g four or five times
+//   with one load in flight: the prior of 131072 positions took 220 us, now
+//   46, of which the g kernel takes 14.) It remains for what
+//   the bins cannot serve: non-finite g, more elements than fit the LDS
+//   arrays, n above kMaxBinned. Digits of 11, 11, 11, 11, 10, 10 bits of the
+//   order-preserving key; as soon as the elements sharing the selected prefix
+//   fit in LDS (<= 4096) they are gathered there; a final pass in index order
+//   writes the selection at offsets from two block scans per 4096 elements.
 
 #include <hip/hip_runtime.h>
 
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "gvr_rope_prior.h"
 
@@ -29,7 +40,9 @@
 
 namespace {
 
-constexpr int kGBlock = 256;                 // threads of a g workgroup
+constexpr int kGBlock = 1024;                // threads of a g workgroup
+constexpr int kGLanes = 4;                   // lanes per position
+constexpr int kGPer = kGBlock / kGLanes;     // positions of a g workgroup
 constexpr int kMaxPairs = 256;               // d <= 512
 constexpr int kSBlock = 1024;                // threads of the select workgroup
 constexpr int kSWaves = kSBlock / 64;
@@ -73,12 +86,13 @@ __global__ __launch_bounds__(kGBlock) void rope_g_kernel(int64_t n, RopeArgs a, 
         if (blockIdx.x == 0 && theta_out) theta_out[t] = v;
     }
     __syncthreads();
-    const int64_t delta = (int64_t)blockIdx.x * kGBlock + t;
-    if (delta >= n) return;
+    const int64_t delta = (int64_t)blockIdx.x * kGPer + t / kGLanes;
     const double x = (double)delta;
     double acc = 0.0;
-    for (int i = 0; i < h; ++i) acc += cos(x * th[i]);
-    g[delta] = 2.0 * acc;
+    for (int i = t % kGLanes; i < h; i += kGLanes) acc += cos(x * th[i]);
+    acc += __shfl_xor(acc, 1, 64);
+    acc += __shfl_xor(acc, 2, 64);
+    if (delta < n && t % kGLanes == 0) g[delta] = 2.0 * acc;
 }
 
 // Order-preserving 64-bit key of a float64 (-0.0 folded into +0.0 first).
@@ -110,17 +124,193 @@ DEV uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
     return base + x - v;
 }
 
+// The binned select (see the file comment). Returns false, with nothing
+// written, where it does not apply; every thread returns the same.
+constexpr int kLinBins = 2048;               // linear bins over [-lim, lim]
+constexpr int kList = 8192;                  // listed elements
+constexpr int kInBin = 1024;                 // elements of the K-th one's bin
+constexpr int kPairs = 8;                    // 16-byte loads in flight per lane
+constexpr int64_t kMaxBinned = (int64_t)kSWaves * 61440;   // a wave's share counts in 16 bits
+struct BinnedSmem {
+    uint32_t hist[kSWaves][kLinBins / 2];    // two 16-bit counts per word
+    uint32_t list[kList];                    // index, bit 31: in the K-th one's bin and not (yet) selected
+    uint64_t key[kInBin];
+    uint32_t pos[kInBin];                    // place in the list
+    uint32_t wcnt[kSWaves];
+    uint32_t wsum[kSWaves];
+    uint32_t bin, above, cnt, fill, bad;
+};
+typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+// v's bin: non-decreasing in v (the conversion and the fused multiply-add round
+// monotonically), any value but NaN clamped into range. In float32, because
+// the float64 form of it took much of both passes (prior at 131072 positions
+// 57.2 -> 53.9 us).
+DEV int lin_bin(float v, float half, float scale) {
+    return min(max((int)__builtin_fmaf(v, scale, half), 0), kLinBins - 1);
+}
+
+// One wave's elements [w0, w1) of g in pairs, kPairs 128-element chunks in
+// flight; body(v, i, full) gets elements i and i + 1, all inside the range if
+// `full` (a compile-time constant), else masked by i < w1 and i + 1 < w1.
+template <typename Body>
+DEV void stream_pairs(const double* __restrict__ g, int n, int w0, int w1, int lane, Body&& body) {
+    int b = w0;
+    for (; b + 128 * kPairs <= w1; b += 128 * kPairs) {
+        const double* gb = g + b + 2 * lane;
+        d2 v[kPairs];
+#pragma unroll
+        for (int u = 0; u < kPairs; ++u) v[u] = *reinterpret_cast<const d2*>(gb + 128 * u);
+#pragma unroll
+        for (int u = 0; u < kPairs; ++u) body(v[u], b + 128 * u + 2 * lane, std::true_type{});
+    }
+    for (; b < w1; b += 128) {
+        const int i = b + 2 * lane;
+        d2 v = *reinterpret_cast<const d2*>(g + min(i, n - 2));   // (n >= 2) the last pair again past the end
+        if (i == n - 1) v.x = v.y;
+        body(v, i, std::false_type{});
+    }
+}
+
+DEV bool binned_select(BinnedSmem& sm, const double* __restrict__ g, int n, int K, float lim,
+                       int32_t* __restrict__ out) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float half = 0.5f * kLinBins, scale = half / lim;
+    const int share = ((n + kSWaves - 1) / kSWaves + 127) / 128 * 128;
+    const int w0 = min(wave * share, n), w1 = min(w0 + share, n);
+    for (int i = tid; i < kSWaves * kLinBins / 2; i += kSBlock) (&sm.hist[0][0])[i] = 0;
+    if (tid == 0) {
+        sm.bad = 0;
+        sm.fill = 0;
+    }
+    __syncthreads();
+    // Pass 1: count every element.
+    uint32_t* const hw = sm.hist[wave];
+    bool bad = false;
+    stream_pairs(g, n, w0, w1, lane, [&](const d2& v, int i, auto full) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float e = (float)(c ? v.y : v.x);
+            if (full.value || i + c < w1) {
+                bad |= e != e;   // NaN: ordered by its sign, not by a bin
+                const int b = lin_bin(e, half, scale);
+                atomicAdd(&hw[b >> 1], 1u << (16 * (b & 1)));
+            }
+        }
+    });
+    if (bad) sm.bad = 1;
+    __syncthreads();
+    if (sm.bad) return false;
+    // Thread t holds bins kLinBins - 1 - 2t and the one below: a scan in
+    // thread order counts the elements in higher bins.
+    const int word = kLinBins / 2 - 1 - tid;   // kSBlock words
+    static_assert(kLinBins / 2 == kSBlock, "one histogram word per thread");
+    uint32_t lo = 0, hi = 0;
+    for (int w = 0; w < kSWaves; ++w) {
+        const uint32_t c = sm.hist[w][word];
+        lo += c & 0xFFFFu;
+        hi += c >> 16;
+    }
+    uint32_t tot;
+    const uint32_t above = block_exclusive_scan(lo + hi, sm.wsum, &tot);
+    const uint32_t k = (uint32_t)K;
+    if (above < k && k <= above + lo + hi) {
+        const bool up = k <= above + hi;
+        sm.bin = (uint32_t)(2 * word + (up ? 1 : 0));
+        sm.above = up ? above : above + hi;
+        sm.cnt = up ? hi : lo;
+    }
+    __syncthreads();
+    const int bin = (int)sm.bin;
+    const uint32_t nab = sm.above, nin = sm.cnt;
+    if (nab + nin > (uint32_t)kList || nin > (uint32_t)kInBin) return false;
+    // Each wave's elements at or above the bin (pairs of bins; the bin's word
+    // counts both of its bins only if it is the lower one).
+    uint32_t mine = 0;
+    for (int j = bin / 2 + lane; j < kLinBins / 2; j += 64) {
+        const uint32_t c = hw[j];
+        mine += (c >> 16) + (2 * j >= bin ? c & 0xFFFFu : 0u);
+    }
+    for (int o = 32; o; o >>= 1) mine += __shfl_xor(mine, o, 64);
+    if (lane == 0) sm.wcnt[wave] = mine;
+    __syncthreads();
+    uint32_t at = 0;
+    for (int w = 0; w < wave; ++w) at += sm.wcnt[w];
+    // Pass 2: list them in index order.
+    const uint64_t below = lane ? ~0ull >> (64 - lane) : 0ull;   // lanes below this one
+    stream_pairs(g, n, w0, w1, lane, [&](const d2& v, int i, auto full) {
+        const int b0 = full.value || i < w1 ? lin_bin((float)v.x, half, scale) : -1;
+        const int b1 = full.value || i + 1 < w1 ? lin_bin((float)v.y, half, scale) : -1;
+        const uint64_t m0 = __ballot(b0 >= bin), m1 = __ballot(b1 >= bin);
+        if (m0 | m1) {   // (wave-uniform)
+            uint32_t p = at + (uint32_t)(__popcll(m0 & below) + __popcll(m1 & below));
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int b = c ? b1 : b0;
+                if (b >= bin) {
+                    sm.list[p] = (uint32_t)(i + c) | (b == bin ? 0x80000000u : 0u);
+                    if (b == bin) {
+                        const uint32_t q = atomicAdd(&sm.fill, 1u);
+                        sm.key[q] = order_key(c ? v.y : v.x);
+                        sm.pos[q] = p;
+                    }
+                    ++p;
+                }
+            }
+            at += (uint32_t)(__popcll(m0) + __popcll(m1));
+        }
+    });
+    __syncthreads();
+    // The bin's elements: the K - nab largest, the lower index first among equals.
+    if (tid < (int)nin) {
+        const uint64_t kk = sm.key[tid];
+        const uint32_t pp = sm.pos[tid];
+        uint32_t before = 0;
+        for (uint32_t j = 0; j < nin; ++j) {
+            const uint64_t o = sm.key[j];
+            before += o > kk || (o == kk && sm.pos[j] < pp);
+        }
+        if (before < k - nab) sm.list[pp] &= 0x7FFFFFFFu;
+    }
+    __syncthreads();
+    constexpr int kPer = kList / kSBlock;
+    const uint32_t m = nab + nin;
+    uint32_t e[kPer], take = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const uint32_t q = (uint32_t)(tid * kPer + j);
+        e[j] = q < m ? sm.list[q] : 0x80000000u;
+        take += !(e[j] >> 31);
+    }
+    uint32_t p = block_exclusive_scan(take, sm.wsum, &tot);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+        if (!(e[j] >> 31)) out[p++] = (int32_t)e[j];
+    return true;
+}
+
 __global__ __launch_bounds__(kSBlock) void prior_select_kernel(const double* __restrict__ g, int64_t n, int K,
-                                                               int32_t* __restrict__ out) {
-    __shared__ uint32_t hist[kSelBins];
-    __shared__ uint64_t cand[kGather];
-    __shared__ uint32_t wsum[kSWaves];
-    __shared__ uint32_t s_bin, s_need, s_cnt, s_ncand;
+                                                               float lim, int32_t* __restrict__ out) {
+    struct RadixSmem {
+        uint32_t hist[kSelBins];
+        uint64_t cand[kGather];
+        uint32_t wsum[kSWaves];
+        uint32_t bin, need, cnt, ncand;
+    };
+    __shared__ union {
+        BinnedSmem b;
+        RadixSmem r;
+    } sm;
+    uint32_t* const hist = sm.r.hist;
+    uint64_t* const cand = sm.r.cand;
+    uint32_t* const wsum = sm.r.wsum;
+    uint32_t &s_bin = sm.r.bin, &s_need = sm.r.need, &s_cnt = sm.r.cnt, &s_ncand = sm.r.ncand;
     const int tid = threadIdx.x;
     if (n <= K) {
         for (int i = tid; i < K; i += kSBlock) out[i] = (i < n) ? i : -1;
         return;
     }
+    if (n <= kMaxBinned && binned_select(sm.b, g, (int)n, K, lim, out)) return;
+    __syncthreads();   // the binned select's arrays are dead
     uint64_t prefix = 0, mask = 0;
     uint32_t need = (uint32_t)K;     // rank of the K-th key among those sharing `prefix`
     uint32_t ncand = 0;
@@ -232,7 +422,7 @@ gvr_status read_params(const gvr_rope_params* p, RopeArgs* a) {
 }
 
 gvr_status launch_g(int64_t n, const RopeArgs& a, double* g, double* theta, void* stream) {
-    const int64_t blocks = n > 0 ? (n + kGBlock - 1) / kGBlock : 1;
+    const int64_t blocks = n > 0 ? (n + kGPer - 1) / kGPer : 1;
     hipLaunchKernelGGL(rope_g_kernel, dim3((unsigned)blocks), dim3(kGBlock), 0, (hipStream_t)stream, n, a, g,
                        theta);
     return hipGetLastError() == hipSuccess ? GVR_OK : GVR_ERR_HIP;
@@ -275,7 +465,7 @@ gvr_status gvr_rope_prior(int64_t n, int32_t K, const gvr_rope_params* params, d
         if (s != GVR_OK) return s;
     }
     hipLaunchKernelGGL(prior_select_kernel, dim3(1), dim3(kSBlock), 0, (hipStream_t)stream, (const double*)g, n,
-                       (int)K, out_delta);
+                       (int)K, (float)a.d, out_delta);
     return hipGetLastError() == hipSuccess ? GVR_OK : GVR_ERR_HIP;
 }
 

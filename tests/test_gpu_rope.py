@@ -202,3 +202,25 @@ def test_gvr_small_batch_split_rows(rows, n):
                      K_TOPK)
     torch.cuda.synchronize()
     assert_rows_equal(got.cpu().numpy(), exp, "gvr_topk small batch rows=%d n=%d" % (rows, n))
+
+
+# (n, K, parameters): the edges of the binned select (K + 1 elements, an odd
+# end, whole 128-element shares, its largest n and one past it) and what it
+# hands to the radix select (an arcsine-like g whose K-th bin is crowded, all
+# values equal, angles that overflow).
+SELECT_CASES = [(2049, 2048, {}), (2051, 2048, {}), (2048 * 16, 2047, {}), (131071, 1, {}), (983040, 2048, {}),
+                (983041, 2048, {}), (50000, 300, {"d_rope": 2}), (400000, 2048, {"d_rope": 2}),
+                (50000, 2048, {"d_rope": 2, "scale": 1e300}), (100003, 777, {"d_rope": 512})]
+
+
+@pytest.mark.parametrize("n,K,kw", SELECT_CASES)
+def test_prior_select_equals_argtopk_of_its_own_g(n, K, kw):
+    """P_static is exactly the K largest of the g the call wrote (the lower
+    Delta first among equals), bit for bit, whichever select ran."""
+    import paper_2604_22312_amd as g
+    gbuf = torch.empty(n, dtype=torch.float64, device=DEV)
+    note("prior select n=%d K=%d %s" % (n, K, kw))
+    out = g.gvr_rope_prior(n, K, params=kw or None, device=DEV, g=gbuf)
+    torch.cuda.synchronize()
+    exp = RP.argtopk(gbuf.cpu().numpy() + 0.0, K)
+    assert_rows_equal(out.cpu().numpy()[None, :], exp[None, :], "prior select n=%d K=%d %s" % (n, K, kw))
