@@ -32,10 +32,13 @@
 //   answer: the row was read once.
 //
 //   Refine (Sec. 4.2.4, Phase 4). One LDS histogram level over the listed
-//   keys (built while the lists are turned into keys), a two-scan bin search
-//   by one wave, then that wave ranks the few keys of the K-th key's bin to
-//   get T* and the per-segment emission offsets (a crowded bin is resolved
-//   from its min / max or narrowed); every key > T* and the first
+//   keys (built while the lists are turned into keys; its total is
+//   f(T_spec)), a bin search (every wave sums its share of the bins into 64
+//   coarse ones, two scans then find the bin), then a rank among the few keys
+//   of the K-th key's bin gives T* and the per-segment emission offsets (a
+//   crowded bin is resolved from its min / max or narrowed); each lane keeps
+//   the first four entries of its wave's list in registers from the copy of
+//   that bin to the emission; every key > T* and the first
 //   K - #{key > T*} keys equal to T* (lower index first) are written out in
 //   ascending index order.
 //

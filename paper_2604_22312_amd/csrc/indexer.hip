@@ -11,7 +11,8 @@
 // [32 (l / 16), + 32) of its head and of its key (a smaller D leaves the upper
 // bytes of the query at zero); in the accumulators it holds heads
 // 4 (l / 16) + i of its key, so the head sum is 4 fused multiply-adds per 16
-// heads plus two exchanges across the four lanes of a key. With this layout a
+// heads plus two row swaps across the four lanes of a key, each serving two
+// tiles or two rows at once. With this layout a
 // 16-byte load of 64 lanes touches 16 cache lines (4 lanes per key row), a
 // quarter of what one key per lane pair would touch.
 //
@@ -21,8 +22,14 @@
 // no branch in the steady state. When the rows of one cache (the draft rows
 // of a request) pair up, one wave serves two of them: each key tile is loaded
 // once and meets both rows' queries (reading it from two waves cost an
-// eighth more time). Bound by HBM: D + 4 bytes per key and cache, 4 bytes
-// written per score.
+// eighth more time).
+//
+// Bound by HBM (D + 4 bytes per key and cache, 4 bytes written per score) as
+// far as the vector work hides behind the loads at two waves per SIMD. The
+// vector instructions per 32 keys and row pair set the rest: accumulators in
+// VGPRs, loads through buffer resources with scalar offsets and head sums by
+// row swaps took them from 290 to 199, and 64 x 2 rows of 100K keys (H = 64,
+// D = 128) from 202.8 us to 189.7 (4.84 TB/s).
 
 #include <hip/hip_runtime.h>
 
@@ -201,6 +208,9 @@ __device__ void sample_guess(const IdxParams& p, int b, float* wl) {
     }
 }
 
+// Two waves per SIMD: with the accumulators in VGPRs a wave needs over 128
+// registers, and the bound keeps the compiler from moving them to AGPRs, from
+// where every epilogue step would copy them back.
 template <int H, int D, int RG>
 __global__ __launch_bounds__(kWaves * kWave, 2) void indexer_kernel(IdxParams p) {
     constexpr int MT = H / 16;   // 16-head row tiles
@@ -320,45 +330,75 @@ __global__ __launch_bounds__(kWaves * kWave, 2) void indexer_kernel(IdxParams p)
         if (u0 + r < tiles) use_slot(ring[r], u0 + r);
 }
 
-// Workgroups of one instance resident on the device at once (0 = unknown:
-// the natural chunk size is used). Queried once per device, never while the
-// stream is being captured into a graph.
+// Compute units, and workgroups of one instance resident on each at once
+// (0 = unknown: the natural chunk size is used). Queried once per device,
+// never while the stream is being captured into a graph.
+struct Resident {
+    int per_cu, cus;
+};
 template <int H, int D, int RG>
-int resident_workgroups(void* stream) {
-    static int cached[64] = {};
+Resident resident_workgroups(void* stream) {
+    static int cached[64] = {};   // per_cu << 16 | cus
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return {0, 0};
     if (cached[dev] == 0) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
-            return 0;
+            return {0, 0};
         int per_cu = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, indexer_kernel<H, D, RG>, kWaves * kWave, 0) != hipSuccess)
-            return 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        cached[dev] = std::max(1, per_cu * cus);
+            return {0, 0};
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return {0, 0};
+        cached[dev] = std::max(1, per_cu) << 16 | std::min(std::max(1, cus), 0xFFFF);
     }
-    return cached[dev];
+    return {cached[dev] >> 16, cached[dev] & 0xFFFF};
+}
+
+// Keys per wave run when the grid is cut for m workgroups on each of `cus`
+// compute units, and the share of those places that the grid fills.
+struct Cut {
+    int run;
+    double fill;
+};
+Cut cut_for(int64_t ld, int64_t caches, int wpr, int64_t slots) {
+    const int64_t natural = (int64_t)wpr * kTilesPerWave * kTile;
+    const int64_t nat = (ld + natural - 1) / natural;
+    const int64_t rounds = std::max<int64_t>(1, nat * caches / slots);
+    const int64_t chunks = std::max<int64_t>(1, rounds * slots / caches);
+    const int64_t per = (ld + chunks - 1) / chunks;                          // keys per chunk
+    const int64_t r = ((per + wpr - 1) / wpr + kTile - 1) / kTile * kTile;   // per wave, whole tiles
+    // At most three natural runs (chunks >= nat / 3 above); the bound keeps a
+    // run's bytes far inside the 32-bit range of its buffer resource.
+    const int run = (int)std::max<int64_t>(std::min<int64_t>(r, 4 * kTilesPerWave * kTile), kMinRun);
+    const int64_t grid = (ld + (int64_t)wpr * run - 1) / ((int64_t)wpr * run) * caches;
+    return {run, (double)grid / ((double)rounds * (double)slots)};
 }
 
 template <int H, int D, int RG>
 gvr_status launch(IdxParams q, int64_t caches, void* stream) {
     // Key chunks per cache. The natural size gives every wave a run of
-    // kTilesPerWave tiles; the grid is then resized to whole rounds of the
-    // workgroups the device holds at once: one round when the natural grid
-    // fits (small batches get finer chunks that reach more compute units, runs
-    // of at least kMinRun keys), else as many full rounds as it fills (no
-    // partly filled last round).
+    // kTilesPerWave tiles; the grid is then resized to whole rounds of m
+    // workgroups per compute unit: one round when the natural grid fits (small
+    // batches get finer chunks that reach more compute units, runs of at least
+    // kMinRun keys), else as many full rounds as it fills (no partly filled
+    // last round). m is the smallest from 2 on that the caches fill to nine
+    // tenths, else the best filled one: fewer workgroups with longer runs pay
+    // the queries and the first loads less often, and places left empty cost
+    // more than that. 40 x 1 rows of 20000 keys (H = 64, D = 128): 18.7 us at
+    // m = 2, 20.9 at 3, 21.3 at 4; 100 x 1 of 30000 50.9 / 57.1 / 57.2; 300 x 1
+    // of 3000, where m = 2 is 59 % full, 29.6 / 25.8 / 23.0.
     const int wpr = q.chunk_keys / (kTilesPerWave * kTile);
     int run = kTilesPerWave * kTile;
-    const int slots = resident_workgroups<H, D, RG>(stream);
-    if (slots > 0) {
-        const int64_t nat = (q.ld + (int64_t)wpr * run - 1) / ((int64_t)wpr * run);
-        const int64_t rounds = std::max<int64_t>(1, nat * caches / slots);
-        const int64_t chunks = std::max<int64_t>(1, rounds * slots / caches);
-        const int64_t per = (q.ld + chunks - 1) / chunks;                        // keys per chunk
-        const int64_t r = ((per + wpr - 1) / wpr + kTile - 1) / kTile * kTile;   // per wave, whole tiles
-        run = (int)std::max<int64_t>(std::min<int64_t>(r, 1 << 24), kMinRun);
+    const Resident res = resident_workgroups<H, D, RG>(stream);
+    if (res.per_cu > 0) {
+        double best = -1.0;
+        for (int m = std::min(2, res.per_cu); m <= res.per_cu && best < 0.9; ++m) {
+            const Cut c = cut_for(q.ld, caches, wpr, (int64_t)m * res.cus);
+            if (c.fill > best) {
+                best = c.fill;
+                run = c.run;
+            }
+        }
     }
     q.run_keys = run;
     q.chunk_keys = wpr * run;
