@@ -51,6 +51,8 @@ constexpr int kTile = 32;                // keys per ring slot (two 16-key matri
 constexpr int kTilesPerWave = 32;        // ring slots of one wave's run (1024 keys)
 constexpr int kRing = 3;                 // key slots held per wave: kRing - 1 in flight while one is used
 constexpr int kMinRun = 8 * kTile;       // shortest wave run the grid sizing picks (256 keys)
+constexpr int kSharedPerCu = 3;          // workgroups per compute unit whose waves share key tiles (see launch)
+constexpr int kSharedLds = 44 * 1024;    // unused LDS that keeps it there (160 KB per compute unit)
 constexpr int64_t kMaxLd = ((int64_t)1 << 31) - 16;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -387,12 +389,23 @@ gvr_status launch(IdxParams q, int64_t caches, void* stream) {
     // more than that. 40 x 1 rows of 20000 keys (H = 64, D = 128): 18.7 us at
     // m = 2, 20.9 at 3, 21.3 at 4; 100 x 1 of 30000 50.9 / 57.1 / 57.2; 300 x 1
     // of 3000, where m = 2 is 59 % full, 29.6 / 25.8 / 23.0.
+    //
+    // Where a cache's rows do not pair (groups of three, and H = 128), several
+    // waves read each key tile, and the reuse is the L1's. With D = 128 more
+    // than three such workgroups per compute unit evict each other's tiles, so
+    // unused LDS keeps it at three and the grid is cut for them (64 x 3 ragged
+    // rows of 60000 keys, H = 32: 135.9 us against 140.7 at four and 147.0
+    // unlimited); with D = 64 every resident workgroup counts (40 x 3 of 20000,
+    // H = 64: 26.5 against 32.5 at m = 2).
     const int wpr = q.chunk_keys / (kTilesPerWave * kTile);
+    const bool shared_tiles = RG == 1 && q.group > 1;
+    const bool limited = shared_tiles && D == 128;
     int run = kTilesPerWave * kTile;
-    const Resident res = resident_workgroups<H, D, RG>(stream);
+    Resident res = resident_workgroups<H, D, RG>(stream);
     if (res.per_cu > 0) {
         double best = -1.0;
-        for (int m = std::min(2, res.per_cu); m <= res.per_cu && best < 0.9; ++m) {
+        if (limited) res.per_cu = std::min(res.per_cu, kSharedPerCu);
+        for (int m = shared_tiles ? res.per_cu : std::min(2, res.per_cu); m <= res.per_cu && best < 0.9; ++m) {
             const Cut c = cut_for(q.ld, caches, wpr, (int64_t)m * res.cus);
             if (c.fill > best) {
                 best = c.fill;
@@ -408,7 +421,8 @@ gvr_status launch(IdxParams q, int64_t caches, void* stream) {
     if (chunks * caches + (q.prev ? q.rows : 0) > 0x7FFFFFFF) return GVR_ERR_TOO_LONG;
     q.sample_base = (int32_t)(chunks * caches);   // the fused guess's workgroups follow the key chunks
     const unsigned grid = (unsigned)(chunks * caches + (q.prev ? q.rows : 0));
-    hipLaunchKernelGGL((indexer_kernel<H, D, RG>), dim3(grid), dim3(kWaves * kWave), 0, (hipStream_t)stream, q);
+    hipLaunchKernelGGL((indexer_kernel<H, D, RG>), dim3(grid), dim3(kWaves * kWave), limited ? kSharedLds : 0, (hipStream_t)stream,
+                       q);
     return hipGetLastError() == hipSuccess ? GVR_OK : GVR_ERR_HIP;
 }
 

@@ -112,6 +112,16 @@ def test_indexer_grid_sizing(requests, group, ld, H, D):
         assert np.all(got[b, n:] == -7.0), "row %d: scores past its length were written" % b
 
 
+@pytest.mark.parametrize("requests,group,ld,H,D", [(60, 3, 3001, 32, 128), (9, 3, 9000, 64, 128), (20, 2, 5003, 128, 128),
+                                                    (300, 1, 3000, 64, 128), (40, 1, 6007, 64, 128),
+                                                    (40, 3, 4099, 64, 64)])
+def test_indexer_grid_cut(requests, group, ld, H, D):
+    """Grids cut for two or more workgroups per compute unit (well and badly
+    filled), and the instances whose waves share key tiles, with and without
+    the limit on resident workgroups."""
+    test_indexer_grid_sizing(requests, group, ld, H, D)
+
+
 def check_topk_exact(got, gpu_scores, rl, K, what):
     """The Top-K the call returned equals the oracle's Top-K over the very
     float32 scores the call wrote, on every row (bit-exact)."""
