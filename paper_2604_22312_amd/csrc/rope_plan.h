@@ -1,0 +1,36 @@
+// rope_plan.h -- host-side planning of the static prior's kernels. Plain C++
+// with no HIP dependency, so the library and a sanitizer build on the CPU
+// compile the same code.
+#ifndef GVR_ROPE_PLAN_H
+#define GVR_ROPE_PLAN_H
+
+#include <stdint.h>
+
+namespace gvr_rope {
+
+constexpr int64_t kMaxN = ((int64_t)1 << 31) - 16;   // longest g (the header's GVR_ERR_TOO_LONG bound)
+
+// The g kernel: kGPer positions per workgroup, one or kGLanes lanes for each.
+constexpr int kGPer = 256;
+constexpr int kGLanes = 4;
+
+struct GLaunch {
+    int lanes;        // lanes per position
+    int64_t blocks;   // workgroups of kGPer * lanes threads
+};
+
+// Four lanes per position while all their waves are resident at once (131072
+// positions are eight waves on each of 1024 SIMDs), and for longer where a
+// position has many pairs; one from there on, and below four pairs, where
+// lanes would idle. Measured (four lanes / one, us): d = 64, 131072 positions
+// 12.7 / 13.9, 196608 18.1 / 17.4, 1048576 81.0 / 65.9; d = 512, 262144
+// 128.1 / 137.1, 800000 398.3 / 391.3; d = 2, 1048576 28.8 / 11.1. A launch's
+// threads must fit 32 bits, which four lanes per position of kMaxN would not.
+inline GLaunch plan_g(int64_t n, int pairs) {
+    const int64_t most = ((int64_t)1 << 17) * (pairs >= 128 ? pairs / 64 : 1);
+    return GLaunch{n <= most && pairs >= kGLanes ? kGLanes : 1, n > 0 ? (n + kGPer - 1) / kGPer : 1};
+}
+
+}  // namespace gvr_rope
+
+#endif  // GVR_ROPE_PLAN_H

@@ -1,14 +1,16 @@
 // rope_prior.hip -- the static RoPE/YaRN prior P_static (Sec. 3.2, 3.3) on
 // MI355X (gfx950), behind the C ABI declared in include/gvr_rope_prior.h.
 //
-//   g kernel. Four lanes per relative position Delta (1024-thread
-//   workgroups, 256 positions each). The first d/2 threads of every workgroup
-//   derive the YaRN angles theta'_i into LDS (a few pow/log calls, the same
-//   in every workgroup), then each lane sums cos(Delta * theta'_i) over every
-//   fourth pair in float64 and the four sums are added as (0 + 1) + (2 + 3).
-//   Bound by the latency of the float64 cosines: one thread per position left
-//   two waves per SIMD at 131072 positions. Run once per model and length,
-//   not per decode step.
+//   g kernel. One or four lanes per relative position Delta (workgroups of
+//   256 positions; rope_plan.h says which). The first d/2 threads of every
+//   workgroup derive the YaRN angles theta'_i into LDS (a few pow/log calls,
+//   the same in every workgroup), then the lanes of a position sum
+//   cos(Delta * theta'_i) in float64, as four sums of every fourth pair added
+//   as (0 + 1) + (2 + 3). Bound by the latency of the float64 cosines until
+//   the positions alone fill the compute units (d = 64: 131072 positions 12.7
+//   us with four lanes each, 13.9 with one), by their rate from there on
+//   (1048576 positions 65.9 us with one lane each, 81.0 with four). Run once
+//   per model and length, not per decode step.
 //
 //   select kernel. One workgroup of 1024 threads, because the calls take no
 //   scratch memory that several could meet in; so it is bound by one compute
@@ -35,14 +37,16 @@
 #include <type_traits>
 
 #include "gvr_rope_prior.h"
+#include "rope_plan.h"
 
 #define DEV __device__ __forceinline__
 
 namespace {
 
-constexpr int kGBlock = 1024;                // threads of a g workgroup
-constexpr int kGLanes = 4;                   // lanes per position
-constexpr int kGPer = kGBlock / kGLanes;     // positions of a g workgroup
+using gvr_rope::kGLanes;
+using gvr_rope::kGPer;
+using gvr_rope::kMaxN;
+
 constexpr int kMaxPairs = 256;               // d <= 512
 constexpr int kSBlock = 1024;                // threads of the select workgroup
 constexpr int kSWaves = kSBlock / 64;
@@ -50,7 +54,6 @@ constexpr int kSelBins = 2048;               // widest digit: 11 bits
 constexpr int kGather = 4096;                // keys the select keeps in LDS
 constexpr int kDigits = 6;
 constexpr int kEmitPer = 4;                  // consecutive elements per thread in the emit pass
-constexpr int64_t kMaxN = ((int64_t)1 << 31) - 16;
 
 __constant__ int kDigitShift[kDigits] = {53, 42, 31, 20, 10, 0};
 __constant__ int kDigitBits[kDigits] = {11, 11, 11, 11, 10, 10};
@@ -75,8 +78,9 @@ DEV double yarn_angle(int i, const RopeArgs& a) {
     return theta * (1.0 - gamma) + (theta / a.scale) * gamma;
 }
 
-__global__ __launch_bounds__(kGBlock) void rope_g_kernel(int64_t n, RopeArgs a, double* __restrict__ g,
-                                                         double* __restrict__ theta_out) {
+template <int LANES>
+__global__ __launch_bounds__(kGPer * LANES) void rope_g_kernel(int64_t n, RopeArgs a, double* __restrict__ g,
+                                                               double* __restrict__ theta_out) {
     __shared__ double th[kMaxPairs];
     const int h = a.d / 2;
     const int t = threadIdx.x;
@@ -86,13 +90,28 @@ __global__ __launch_bounds__(kGBlock) void rope_g_kernel(int64_t n, RopeArgs a, 
         if (blockIdx.x == 0 && theta_out) theta_out[t] = v;
     }
     __syncthreads();
-    const int64_t delta = (int64_t)blockIdx.x * kGPer + t / kGLanes;
+    const int64_t delta = (int64_t)blockIdx.x * kGPer + t / LANES;
     const double x = (double)delta;
+    // Four sums, of every fourth pair each, added as (0 + 1) + (2 + 3) in both
+    // forms: g(Delta) is the same bits for every n.
+    auto every_fourth = [&](int q) {
+        double acc = 0.0;
+        for (int i = q; i < h; i += kGLanes) acc += cos(x * th[i]);
+        return acc;
+    };
     double acc = 0.0;
-    for (int i = t % kGLanes; i < h; i += kGLanes) acc += cos(x * th[i]);
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    if (delta < n && t % kGLanes == 0) g[delta] = 2.0 * acc;
+    if constexpr (LANES == kGLanes) {
+        acc = every_fourth(t % kGLanes);
+        acc += __shfl_xor(acc, 1, 64);
+        acc += __shfl_xor(acc, 2, 64);
+    } else {
+#pragma unroll 1
+        for (int q = 0; q < kGLanes && q < h; q += 2) {
+            const double even = every_fourth(q);
+            acc += even + every_fourth(q + 1);
+        }
+    }
+    if (delta < n && t % LANES == 0) g[delta] = 2.0 * acc;
 }
 
 // Order-preserving 64-bit key of a float64 (-0.0 folded into +0.0 first).
@@ -422,9 +441,12 @@ gvr_status read_params(const gvr_rope_params* p, RopeArgs* a) {
 }
 
 gvr_status launch_g(int64_t n, const RopeArgs& a, double* g, double* theta, void* stream) {
-    const int64_t blocks = n > 0 ? (n + kGPer - 1) / kGPer : 1;
-    hipLaunchKernelGGL(rope_g_kernel, dim3((unsigned)blocks), dim3(kGBlock), 0, (hipStream_t)stream, n, a, g,
-                       theta);
+    const gvr_rope::GLaunch p = gvr_rope::plan_g(n, a.d / 2);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)p.blocks), dim3((unsigned)(kGPer * p.lanes)), 0, (hipStream_t)stream,
+                           n, a, g, theta);
+    };
+    p.lanes == kGLanes ? launch(rope_g_kernel<kGLanes>) : launch(rope_g_kernel<1>);
     return hipGetLastError() == hipSuccess ? GVR_OK : GVR_ERR_HIP;
 }
 

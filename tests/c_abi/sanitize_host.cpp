@@ -2,7 +2,8 @@
 // (g++ / gcc, no GPU code): the host-side planning of a Top-K call
 // (paper_2604_22312_amd/csrc/host_plan.h: argument checks, workgroup shape
 // and row split, workspace layout, the per-stream workspace cache with its
-// growth and keep-alive rule) and the C oracle (oracle/oracle_topk.c) against
+// growth and keep-alive rule) and of the static prior (csrc/rope_plan.h), and
+// the C oracle (oracle/oracle_topk.c) against
 // a brute-force full sort on tie-heavy rows with special values. Prints "ok".
 #include <stdio.h>
 #include <stdlib.h>
@@ -15,6 +16,7 @@
 #include <vector>
 
 #include "host_plan.h"
+#include "rope_plan.h"
 
 extern "C" int oracle_topk(const float* scores, int64_t B, int64_t ld, const int32_t* row_len, int32_t K,
                            int32_t* out_idx, uint32_t* kth_key, int32_t* n_gt);
@@ -181,6 +183,23 @@ static void check_workspace() {
     g_capturing = false;
 }
 
+static void check_rope_plan() {
+    using namespace gvr_rope;
+    // every length the entry points take is one launch whose threads fit 32
+    // bits, covers each position and leaves less than one workgroup over
+    for (int64_t n : {(int64_t)0, (int64_t)1, (int64_t)256, (int64_t)257, (int64_t)131072, (int64_t)131073,
+                      (int64_t)524289, (int64_t)1073741568, (int64_t)1073741569, (int64_t)1 << 30, kMaxN})
+        for (int pairs : {1, 3, 4, 32, 64, 128, 256}) {
+            const GLaunch p = plan_g(n, pairs);
+            CHECK((p.lanes == 1 || p.lanes == kGLanes) && p.blocks >= 1);
+            CHECK(p.blocks * kGPer * p.lanes <= (int64_t)0xFFFFFFFF);
+            CHECK(p.blocks * kGPer >= n && (p.blocks - 1) * kGPer <= n);
+            CHECK(p.lanes == 1 || pairs >= kGLanes);
+        }
+    CHECK(plan_g(131072, 32).lanes == kGLanes && plan_g(131073, 32).lanes == 1);
+    CHECK(plan_g(524288, 256).lanes == kGLanes && plan_g(524289, 256).lanes == 1);
+}
+
 static uint32_t key_of(float x) {
     uint32_t u;
     memcpy(&u, &x, 4);
@@ -226,6 +245,7 @@ int main() {
     check_validate();
     check_plans();
     check_workspace();
+    check_rope_plan();
     check_oracle();
     printf("ok\n");
     return 0;

@@ -67,6 +67,36 @@ def test_rope_g_matches_oracle(name, kw, n):
     assert err <= g_tol(n, d), (err, g_tol(n, d))
 
 
+@pytest.mark.parametrize("d", [2, 6, 8, 10, 64, 512])
+def test_rope_g_is_the_same_for_every_length(d):
+    """g(Delta) is the same bits whether one lane or four serve a position."""
+    import paper_2604_22312_amd as g
+    note("gvr_rope_g d=%d around the change of lanes" % d)
+    short = g.gvr_rope_g(131072, {"d_rope": d}, device=DEV)
+    longer = g.gvr_rope_g(131073, {"d_rope": d}, device=DEV)
+    longest = g.gvr_rope_g(524289, {"d_rope": d}, device=DEV)
+    torch.cuda.synchronize()
+    th_o, _ = oracle_theta({"d_rope": d})
+    bits = lambda t: t.view(torch.int64)  # noqa: E731
+    assert torch.equal(bits(short), bits(longer)[:131072])
+    assert torch.equal(bits(longer), bits(longest)[:131073])
+    assert np.max(np.abs(longest.cpu().numpy() - RP.g_delta(524289, th_o))) <= g_tol(524289, d)
+
+
+def test_rope_g_past_a_launch_of_four_lanes():
+    """Lengths whose positions at four lanes each would exceed a launch's 2^32 - 1 threads."""
+    import paper_2604_22312_amd as g
+    n = (1 << 30) + 300
+    note("gvr_rope_g n=%d" % n)
+    got = g.gvr_rope_g(n, device=DEV)
+    torch.cuda.synchronize()
+    th_o, d = oracle_theta({})
+    for at in (0, 1073741568 - 500, n - 1000):
+        delta = np.arange(at, at + 1000, dtype=np.float64)
+        ref = 2.0 * np.cos(np.outer(delta, th_o)).sum(axis=1)
+        assert np.max(np.abs(got[at:at + 1000].cpu().numpy() - ref)) <= g_tol(n, d), at
+
+
 def check_prior(got, n, K, th_o, d):
     exp = RP.static_prior(n, K, th_o)
     if np.array_equal(got, exp):
