@@ -1,6 +1,6 @@
-// rope_plan.h -- host-side planning of the static prior's kernels. Plain C++
-// with no HIP dependency, so the library and a sanitizer build on the CPU
-// compile the same code.
+// rope_plan.h -- planning of the static prior's kernels and the select's
+// linear bins. Plain C++ with no HIP dependency, so the library and a
+// sanitizer build on the CPU compile the same code.
 #ifndef GVR_ROPE_PLAN_H
 #define GVR_ROPE_PLAN_H
 
@@ -29,6 +29,17 @@ struct GLaunch {
 inline GLaunch plan_g(int64_t n, int pairs) {
     const int64_t most = ((int64_t)1 << 17) * (pairs >= 128 ? pairs / 64 : 1);
     return GLaunch{n <= most && pairs >= kGLanes ? kGLanes : 1, n > 0 ? (n + kGPer - 1) / kGPer : 1};
+}
+
+// v's bin among kLinBins linear ones over [-lim, lim], with half = kLinBins / 2
+// and scale = half / lim: non-decreasing in v (the fused multiply-add rounds
+// monotonically), anything outside clamped, NaN in bin 0. Clamped before the
+// conversion, which is undefined outside int's range. In float32, because the
+// float64 form took much of both passes (prior at 131072 positions 57.2 ->
+// 53.9 us).
+constexpr int kLinBins = 2048;
+inline int lin_bin(float v, float half, float scale) {
+    return (int)__builtin_fminf(__builtin_fmaxf(__builtin_fmaf(v, scale, half), 0.f), (float)(kLinBins - 1));
 }
 
 }  // namespace gvr_rope

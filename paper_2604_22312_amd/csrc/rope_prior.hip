@@ -37,7 +37,9 @@
 #include <type_traits>
 
 #include "gvr_rope_prior.h"
+#pragma clang force_cuda_host_device begin
 #include "rope_plan.h"
+#pragma clang force_cuda_host_device end
 
 #define DEV __device__ __forceinline__
 
@@ -45,7 +47,9 @@ namespace {
 
 using gvr_rope::kGLanes;
 using gvr_rope::kGPer;
+using gvr_rope::kLinBins;
 using gvr_rope::kMaxN;
+using gvr_rope::lin_bin;
 
 constexpr int kMaxPairs = 256;               // d <= 512
 constexpr int kSBlock = 1024;                // threads of the select workgroup
@@ -145,7 +149,6 @@ DEV uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
 
 // The binned select (see the file comment). Returns false, with nothing
 // written, where it does not apply; every thread returns the same.
-constexpr int kLinBins = 2048;               // linear bins over [-lim, lim]
 constexpr int kList = 8192;                  // listed elements
 constexpr int kInBin = 1024;                 // elements of the K-th one's bin
 constexpr int kPairs = 8;                    // 16-byte loads in flight per lane
@@ -160,13 +163,6 @@ struct BinnedSmem {
     uint32_t bin, above, cnt, fill, bad;
 };
 typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
-// v's bin: non-decreasing in v (the conversion and the fused multiply-add round
-// monotonically), any value but NaN clamped into range. In float32, because
-// the float64 form of it took much of both passes (prior at 131072 positions
-// 57.2 -> 53.9 us).
-DEV int lin_bin(float v, float half, float scale) {
-    return min(max((int)__builtin_fmaf(v, scale, half), 0), kLinBins - 1);
-}
 
 // One wave's elements [w0, w1) of g in pairs, kPairs 128-element chunks in
 // flight; body(v, i, full) gets elements i and i + 1, all inside the range if

@@ -200,6 +200,27 @@ static void check_rope_plan() {
     CHECK(plan_g(524288, 256).lanes == kGLanes && plan_g(524289, 256).lanes == 1);
 }
 
+static void check_lin_bin() {
+    using namespace gvr_rope;
+    const float inf = std::numeric_limits<float>::infinity();
+    for (float lim : {2.f, 64.f, 512.f}) {
+        const float half = 0.5f * kLinBins, scale = half / lim;
+        auto bin = [&](float v) { return lin_bin(v, half, scale); };
+        CHECK(bin(-lim) == 0 && bin(lim) == kLinBins - 1 && bin(0.f) == kLinBins / 2);
+        // outside int's range, where a conversion ahead of the clamp is undefined
+        CHECK(bin(inf) == kLinBins - 1 && bin(1e30f) == kLinBins - 1);
+        CHECK(bin(-inf) == 0 && bin(-1e30f) == 0);
+        CHECK(bin(std::numeric_limits<float>::quiet_NaN()) == 0);
+        int last = 0;
+        for (int i = -40000; i <= 40000; ++i) {
+            const float v = lim * (float)i / 32768.f;
+            CHECK(bin(v) >= last && bin(v) < kLinBins);
+            CHECK(bin(v) == std::min(std::max((int)std::fma(v, scale, half), 0), kLinBins - 1));
+            last = bin(v);
+        }
+    }
+}
+
 static uint32_t key_of(float x) {
     uint32_t u;
     memcpy(&u, &x, 4);
@@ -246,6 +267,7 @@ int main() {
     check_plans();
     check_workspace();
     check_rope_plan();
+    check_lin_bin();
     check_oracle();
     printf("ok\n");
     return 0;

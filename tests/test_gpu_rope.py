@@ -234,17 +234,47 @@ def test_gvr_small_batch_split_rows(rows, n):
     assert_rows_equal(got.cpu().numpy(), exp, "gvr_topk small batch rows=%d n=%d" % (rows, n))
 
 
-# (n, K, parameters): the edges of the binned select (K + 1 elements, an odd
-# end, whole 128-element shares, its largest n and one past it) and what it
-# hands to the radix select (an arcsine-like g whose K-th bin is crowded, all
-# values equal, angles that overflow).
-SELECT_CASES = [(2049, 2048, {}), (2051, 2048, {}), (2048 * 16, 2047, {}), (131071, 1, {}), (983040, 2048, {}),
-                (983041, 2048, {}), (50000, 300, {"d_rope": 2}), (400000, 2048, {"d_rope": 2}),
-                (50000, 2048, {"d_rope": 2, "scale": 1e300}), (100003, 777, {"d_rope": 512})]
+# (n, K, parameters, what g is): the edges of the binned select (K + 1
+# elements, an odd end, whole 128-element shares, its largest n and one past
+# it) and what only the radix select can serve: a K-th bin with more elements
+# than are ranked at once (one rotary pair's g is arcsine-distributed), NaN
+# from angles that overflow, for every Delta (every key equal) or from some
+# Delta on.
+SELECT_CASES = [(2049, 2048, {}, "binned"), (2051, 2048, {}, "binned"), (2048 * 16, 2047, {}, "binned"),
+                (131071, 1, {}, "binned"), (983040, 2048, {}, "binned"), (983041, 2048, {}, "long"),
+                (50000, 300, {"d_rope": 2}, "binned"), (400000, 2048, {"d_rope": 2}, "crowded"),
+                (100000, 1, {"d_rope": 2}, "crowded"), (72704, 1025, {"d_rope": 2}, "binned"),
+                (50000, 2048, {"d_rope": 2, "scale": 1e300}, "binned"), (100003, 777, {"d_rope": 512}, "binned"),
+                (5000, 2048, {"d_rope": 2, "base": 1e300, "scale": 1e-320}, "all NaN"),
+                (40000, 2048, {"d_rope": 4, "scale": 1e-306}, "some NaN"),
+                (36500, 2048, {"d_rope": 4, "scale": 1e-306}, "some NaN")]
 
 
-@pytest.mark.parametrize("n,K,kw", SELECT_CASES)
-def test_prior_select_equals_argtopk_of_its_own_g(n, K, kw):
+def order_keys(g):
+    """The 64-bit order-preserving keys of float64 values (NaN by its sign)."""
+    u = (g + 0.0).view(np.uint64)
+    return np.where(u >> np.uint64(63), ~u, u | np.uint64(1 << 63))
+
+
+def check_select_case(g, K, d, what):
+    """The case is what it says: which select can serve it follows from g."""
+    nan = np.isnan(g)
+    assert (what == "all NaN") == bool(nan.all()) and (what == "some NaN") == bool(nan.any() and not nan.all())
+    if nan.any():
+        return
+    if what == "long":
+        assert len(g) > 983040
+        return
+    bins = 2048   # linear ones over [-d, d]
+    b = np.clip(np.floor(g * (bins / 2 / d) + bins / 2).astype(np.int64), 0, bins - 1)
+    count = np.bincount(b, minlength=bins)
+    from_top = np.cumsum(count[::-1])[::-1]
+    kth = np.max(np.nonzero(from_top >= K)[0])
+    assert (count[kth] > 1024) == (what == "crowded"), (kth, count[kth])
+
+
+@pytest.mark.parametrize("n,K,kw,what", SELECT_CASES)
+def test_prior_select_equals_argtopk_of_its_own_g(n, K, kw, what):
     """P_static is exactly the K largest of the g the call wrote (the lower
     Delta first among equals), bit for bit, whichever select ran."""
     import paper_2604_22312_amd as g
@@ -252,5 +282,9 @@ def test_prior_select_equals_argtopk_of_its_own_g(n, K, kw):
     note("prior select n=%d K=%d %s" % (n, K, kw))
     out = g.gvr_rope_prior(n, K, params=kw or None, device=DEV, g=gbuf)
     torch.cuda.synchronize()
-    exp = RP.argtopk(gbuf.cpu().numpy() + 0.0, K)
+    gv = gbuf.cpu().numpy()
+    check_select_case(gv, K, kw.get("d_rope", 64), what)
+    exp = np.sort(np.argsort(~order_keys(gv), kind="stable")[:K]).astype(np.int32)
+    if not np.isnan(gv).any():
+        assert np.array_equal(exp, RP.argtopk(gv + 0.0, K))
     assert_rows_equal(out.cpu().numpy()[None, :], exp[None, :], "prior select n=%d K=%d %s" % (n, K, kw))
