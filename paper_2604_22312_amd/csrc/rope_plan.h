@@ -38,6 +38,7 @@ inline GLaunch plan_g(int64_t n, int pairs) {
 // float64 form took much of both passes (prior at 131072 positions 57.2 ->
 // 53.9 us).
 constexpr int kLinBins = 2048;
+constexpr int kInBin = 1024;   // most elements of the K-th one's bin
 inline int lin_bin(float v, float half, float scale) {
     return (int)__builtin_fminf(__builtin_fmaxf(__builtin_fmaf(v, scale, half), 0.f), (float)(kLinBins - 1));
 }

@@ -23,8 +23,8 @@
 //   indices. (A radix select over the 64-bit keys read g four or five times
 //   with one load in flight: the prior of 131072 positions took 220 us, now
 //   46, of which the g kernel takes 14.) It remains for what
-//   the bins cannot serve: non-finite g, more elements than fit the LDS
-//   arrays, n above kMaxBinned. Digits of 11, 11, 11, 11, 10, 10 bits of the
+//   the bins cannot serve: non-finite g, more than kInBin elements in the
+//   K-th one's bin, n above kMaxBinned. Digits of 11, 11, 11, 11, 10, 10 bits of the
 //   order-preserving key; as soon as the elements sharing the selected prefix
 //   fit in LDS (<= 4096) they are gathered there; a final pass in index order
 //   writes the selection at offsets from two block scans per 4096 elements.
@@ -47,6 +47,7 @@ namespace {
 
 using gvr_rope::kGLanes;
 using gvr_rope::kGPer;
+using gvr_rope::kInBin;
 using gvr_rope::kLinBins;
 using gvr_rope::kMaxN;
 using gvr_rope::lin_bin;
@@ -149,8 +150,7 @@ DEV uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
 
 // The binned select (see the file comment). Returns false, with nothing
 // written, where it does not apply; every thread returns the same.
-constexpr int kList = 8192;                  // listed elements
-constexpr int kInBin = 1024;                 // elements of the K-th one's bin
+constexpr int kList = GVR_MAX_K + kInBin;    // listed: fewer than K above the K-th one's bin, and the bin
 constexpr int kPairs = 8;                    // 16-byte loads in flight per lane
 constexpr int64_t kMaxBinned = (int64_t)kSWaves * 61440;   // a wave's share counts in 16 bits
 struct BinnedSmem {
@@ -237,7 +237,7 @@ DEV bool binned_select(BinnedSmem& sm, const double* __restrict__ g, int n, int 
     __syncthreads();
     const int bin = (int)sm.bin;
     const uint32_t nab = sm.above, nin = sm.cnt;
-    if (nab + nin > (uint32_t)kList || nin > (uint32_t)kInBin) return false;
+    if (nin > (uint32_t)kInBin) return false;   // (nab < K)
     // Each wave's elements at or above the bin (pairs of bins; the bin's word
     // counts both of its bins only if it is the lower one).
     uint32_t mine = 0;
@@ -287,6 +287,7 @@ DEV bool binned_select(BinnedSmem& sm, const double* __restrict__ g, int n, int 
         if (before < k - nab) sm.list[pp] &= 0x7FFFFFFFu;
     }
     __syncthreads();
+    static_assert(kList % kSBlock == 0, "whole list entries per thread");
     constexpr int kPer = kList / kSBlock;
     const uint32_t m = nab + nin;
     uint32_t e[kPer], take = 0;
