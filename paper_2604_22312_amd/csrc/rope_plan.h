@@ -43,6 +43,23 @@ inline int lin_bin(float v, float half, float scale) {
     return (int)__builtin_fminf(__builtin_fmaxf(__builtin_fmaf(v, scale, half), 0.f), (float)(kLinBins - 1));
 }
 
+// Whether the binned select can serve a call: a wave's share must count in 16
+// bits, and the K-th one's bin must hold at most kInBin elements, or a whole
+// pass over g is spent before the radix select runs. That fails for finite g
+// with one rotary pair (d = 2): g = 2 cos is crowded at its ends, its top bin
+// holds acos(1 - 2 / (kLinBins / 2)) / pi = 1 / 71 of the positions, and once
+// that is more than kInBin the bin below, 1 / 172 of them, is too, unless it
+// lies above K. (K = 2048, radix / binned and then radix, us: 400000
+// positions 516 / 565, 900000 1846 / 1953; the binned select alone at 131072:
+// 107 against 175.) With more pairs the ends are thin.
+constexpr int kSelectWaves = 16;
+constexpr int64_t kMaxBinned = (int64_t)kSelectWaves * 61440;
+inline bool binned_serves(int64_t n, int K, int pairs) {
+    if (n > kMaxBinned) return false;
+    const int64_t top = n / 71;   // of one pair
+    return pairs > 1 || top <= kInBin || top < K;
+}
+
 }  // namespace gvr_rope
 
 #endif  // GVR_ROPE_PLAN_H

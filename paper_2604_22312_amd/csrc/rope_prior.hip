@@ -23,8 +23,8 @@
 //   indices. (A radix select over the 64-bit keys read g four or five times
 //   with one load in flight: the prior of 131072 positions took 220 us, now
 //   46, of which the g kernel takes 14.) It remains for what
-//   the bins cannot serve: non-finite g, more than kInBin elements in the
-//   K-th one's bin, n above kMaxBinned. Digits of 11, 11, 11, 11, 10, 10 bits of the
+//   the bins cannot serve (binned_serves of rope_plan.h says what is known
+//   ahead; the rest, NaN among it, is found by the first pass). Digits of 11, 11, 11, 11, 10, 10 bits of the
 //   order-preserving key; as soon as the elements sharing the selected prefix
 //   fit in LDS (<= 4096) they are gathered there; a final pass in index order
 //   writes the selection at offsets from two block scans per 4096 elements.
@@ -152,7 +152,7 @@ DEV uint32_t block_exclusive_scan(uint32_t v, uint32_t* wsum, uint32_t* total) {
 // written, where it does not apply; every thread returns the same.
 constexpr int kList = GVR_MAX_K + kInBin;    // listed: fewer than K above the K-th one's bin, and the bin
 constexpr int kPairs = 8;                    // 16-byte loads in flight per lane
-constexpr int64_t kMaxBinned = (int64_t)kSWaves * 61440;   // a wave's share counts in 16 bits
+static_assert(kSWaves == gvr_rope::kSelectWaves, "a wave's share counts in 16 bits");
 struct BinnedSmem {
     uint32_t hist[kSWaves][kLinBins / 2];    // two 16-bit counts per word
     uint32_t list[kList];                    // index, bit 31: in the K-th one's bin and not (yet) selected
@@ -304,6 +304,9 @@ DEV bool binned_select(BinnedSmem& sm, const double* __restrict__ g, int n, int 
     return true;
 }
 
+// BINNED: the binned select, and the radix select where it gives up; else the
+// radix select alone.
+template <bool BINNED>
 __global__ __launch_bounds__(kSBlock) void prior_select_kernel(const double* __restrict__ g, int64_t n, int K,
                                                                float lim, int32_t* __restrict__ out) {
     struct RadixSmem {
@@ -312,21 +315,28 @@ __global__ __launch_bounds__(kSBlock) void prior_select_kernel(const double* __r
         uint32_t wsum[kSWaves];
         uint32_t bin, need, cnt, ncand;
     };
-    __shared__ union {
+    union BothSmem {
         BinnedSmem b;
         RadixSmem r;
-    } sm;
-    uint32_t* const hist = sm.r.hist;
-    uint64_t* const cand = sm.r.cand;
-    uint32_t* const wsum = sm.r.wsum;
-    uint32_t &s_bin = sm.r.bin, &s_need = sm.r.need, &s_cnt = sm.r.cnt, &s_ncand = sm.r.ncand;
+    };
+    __shared__ std::conditional_t<BINNED, BothSmem, RadixSmem> sm;
+    RadixSmem& r = [&]() -> RadixSmem& {
+        if constexpr (BINNED) return sm.r;
+        else return sm;
+    }();
+    uint32_t* const hist = r.hist;
+    uint64_t* const cand = r.cand;
+    uint32_t* const wsum = r.wsum;
+    uint32_t &s_bin = r.bin, &s_need = r.need, &s_cnt = r.cnt, &s_ncand = r.ncand;
     const int tid = threadIdx.x;
     if (n <= K) {
         for (int i = tid; i < K; i += kSBlock) out[i] = (i < n) ? i : -1;
         return;
     }
-    if (n <= kMaxBinned && binned_select(sm.b, g, (int)n, K, lim, out)) return;
-    __syncthreads();   // the binned select's arrays are dead
+    if constexpr (BINNED) {
+        if (binned_select(sm.b, g, (int)n, K, lim, out)) return;
+        __syncthreads();   // the binned select's arrays are dead
+    }
     uint64_t prefix = 0, mask = 0;
     uint32_t need = (uint32_t)K;     // rank of the K-th key among those sharing `prefix`
     uint32_t ncand = 0;
@@ -483,8 +493,9 @@ gvr_status gvr_rope_prior(int64_t n, int32_t K, const gvr_rope_params* params, d
         const gvr_status s = launch_g(n, a, g, nullptr, stream);
         if (s != GVR_OK) return s;
     }
-    hipLaunchKernelGGL(prior_select_kernel, dim3(1), dim3(kSBlock), 0, (hipStream_t)stream, (const double*)g, n,
-                       (int)K, (float)a.d, out_delta);
+    const bool binned = gvr_rope::binned_serves(n, K, a.d / 2);
+    hipLaunchKernelGGL(binned ? prior_select_kernel<true> : prior_select_kernel<false>, dim3(1), dim3(kSBlock), 0,
+                       (hipStream_t)stream, (const double*)g, n, (int)K, (float)a.d, out_delta);
     return hipGetLastError() == hipSuccess ? GVR_OK : GVR_ERR_HIP;
 }
 

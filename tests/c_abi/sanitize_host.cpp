@@ -221,6 +221,27 @@ static void check_lin_bin() {
     }
 }
 
+// The rule of the binned select against the bins themselves: with one rotary
+// pair it is used exactly where the K-th element's bin holds at most kInBin
+// (one part in sixteen left open at the line, which the count's own noise moves).
+static void check_binned_serves() {
+    using namespace gvr_rope;
+    CHECK(binned_serves(kMaxBinned, 2048, 32) && !binned_serves(kMaxBinned + 1, 2048, 32));
+    for (int64_t n : {3000, 50000, 70000, 80000, 131072, 140000, 160000, 400000, 983040}) {
+        std::vector<int64_t> count(kLinBins, 0);
+        for (int64_t i = 0; i < n; ++i) ++count[lin_bin((float)(2.0 * std::cos((double)i)), 0.5f * kLinBins, 0.25f * kLinBins)];
+        for (int K : {1, 16, 300, 1024, 1500, 2048}) {
+            if (n <= K) continue;
+            int64_t above = 0;
+            int b = kLinBins - 1;
+            while (above + count[b] < K) above += count[b--];
+            const bool fits = count[b] <= kInBin;
+            const bool at_line = std::abs(n / 71 - (n / 71 < 1100 ? kInBin : K)) * 16 < std::max<int64_t>(kInBin, K);
+            CHECK(at_line || binned_serves(n, K, 1) == fits);
+        }
+    }
+}
+
 static uint32_t key_of(float x) {
     uint32_t u;
     memcpy(&u, &x, 4);
@@ -268,6 +289,7 @@ int main() {
     check_workspace();
     check_rope_plan();
     check_lin_bin();
+    check_binned_serves();
     check_oracle();
     printf("ok\n");
     return 0;
