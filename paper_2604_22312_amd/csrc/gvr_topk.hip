@@ -592,7 +592,7 @@ constexpr int kMaxSnap = 64;
 template <int NW>
 DEV uint32_t paper_refine_emit(Smem<NW>& sm, int K, int32_t* out, int tid, int* n_gt_out, int* snaps_out) {
     using W = Shape<NW>;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // (4a) min / max
     uint32_t mn = 0xFFFFFFFFu, mx = 0u;
     for_my_keys(sm, wave, lane, [&](uint32_t kk) {
@@ -625,20 +625,35 @@ DEV uint32_t paper_refine_emit(Smem<NW>& sm, int K, int32_t* out, int tid, int* 
         if (lane == 0) sm.wa[wave] = t;
     }
     lds_barrier();
-    if (tid == 0) {   // target wave: one serial step per wave from the top
+    // The serial scans, by a whole wave whose lanes read the same word: counts
+    // in SGPRs keep each step's branch scalar (one lane alone, its loop masked
+    // by exec, took more or less time per step with the code around it).
+    if (wave == 0) {   // target wave: one serial step per wave from the top
         int run = 0, w = 0;
-        for (; w < NW - 1 && run + sm.wa[w] < K; ++w) run += sm.wa[w];
-        sm.scal[0] = w;
-        sm.scal[1] = run;
+        for (; w < NW - 1; ++w) {
+            const int h = __builtin_amdgcn_readfirstlane(sm.wa[w]);
+            if (run + h >= K) break;
+            run += h;
+        }
+        if (lane == 0) {
+            sm.scal[0] = w;
+            sm.scal[1] = run;
+        }
     }
     lds_barrier();
-    if (wave == sm.scal[0] && lane == 0) {   // exact bin: up to kPerWave serial steps from the top of the wave's bins
-        int run = sm.scal[1];
+    if (wave == __builtin_amdgcn_readfirstlane(sm.scal[0])) {   // exact bin: up to kPerWave serial steps from the top of the wave's bins
+        int run = __builtin_amdgcn_readfirstlane(sm.scal[1]);
         int b = kPaperBins - kPerWave * wave - 1;
         const int bend = kPaperBins - kPerWave * (wave + 1);
-        for (; b > bend && run + sm.u.rhist[b] < K; --b) run += sm.u.rhist[b];
-        sm.scal[2] = b;
-        sm.scal[3] = run;
+        for (; b > bend; --b) {
+            const int h = __builtin_amdgcn_readfirstlane(sm.u.rhist[b]);
+            if (run + h >= K) break;
+            run += h;
+        }
+        if (lane == 0) {
+            sm.scal[2] = b;
+            sm.scal[3] = run;
+        }
     }
     lds_barrier();
     const int kb = sm.scal[2];
