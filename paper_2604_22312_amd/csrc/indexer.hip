@@ -40,6 +40,9 @@
 #include "gvr_indexer.h"
 #include "guess.h"
 #include "host_plan.h"
+#pragma clang force_cuda_host_device begin
+#include "indexer_plan.h"
+#pragma clang force_cuda_host_device end
 #include "topk_internal.h"
 
 namespace {
@@ -47,12 +50,10 @@ namespace {
 using namespace gvr_dev;
 
 constexpr int kWaves = 4;                // waves per workgroup
-constexpr int kTile = 32;                // keys per ring slot (two 16-key matrix tiles)
-constexpr int kTilesPerWave = 32;        // ring slots of one wave's run (1024 keys)
+using gvr_idx::kTile;
+using gvr_idx::kTilesPerWave;
 constexpr int kRing = 3;                 // key slots held per wave: kRing - 1 in flight while one is used
-constexpr int kMinRun = 8 * kTile;       // shortest wave run the grid sizing picks (256 keys)
-constexpr int kSharedPerCu = 3;          // workgroups per compute unit whose waves share key tiles (see launch)
-constexpr int kSharedLds = 44 * 1024;    // unused LDS that keeps it there (160 KB per compute unit)
+constexpr int kSharedLds = 44 * 1024;    // unused LDS that keeps a grid at kSharedPerCu (160 KB per compute unit)
 constexpr int64_t kMaxLd = ((int64_t)1 << 31) - 16;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -74,6 +75,7 @@ struct IdxParams {
     int32_t chunks;       // workgroups per cache (key chunks)
     int32_t chunk_keys;   // keys per workgroup chunk
     int32_t run_keys;     // keys per wave run (a multiple of kTile)
+    gvr_idx::Rotation rot;
     // Fused guess (gvr_indexer_topk): workgroups [sample_base, + rows) score
     // the keys at row b's strided sample of prev [rows][K] and write the
     // sample's GuessStats words to gstats + b * K. prev NULL: none.
@@ -231,7 +233,8 @@ __global__ __launch_bounds__(kWaves * kWave, 2) void indexer_kernel(IdxParams p)
     const int wpr = kWaves / slots;           // waves per row slot (one idle wave when G = 3)
     if (wave >= slots * wpr) return;
     const int g = blockIdx.x / p.chunks;      // cache
-    const int c = blockIdx.x - g * p.chunks;  // key chunk
+    int c = blockIdx.x - g * p.chunks + gvr_idx::first_chunk(g, p.rot.shift, p.rot.mask, p.rot.step);   // key chunk
+    if (c >= p.chunks) c -= p.chunks;
     const int slot_i = wave % slots, sub = wave / slots;
     const int64_t row0 = (int64_t)g * G + slot_i * RG;
     if (row0 >= p.rows) return;
@@ -356,72 +359,22 @@ Resident resident_workgroups(void* stream) {
     return {cached[dev] >> 16, cached[dev] & 0xFFFF};
 }
 
-// Keys per wave run when the grid is cut for m workgroups on each of `cus`
-// compute units, and the share of those places that the grid fills.
-struct Cut {
-    int run;
-    double fill;
-};
-Cut cut_for(int64_t ld, int64_t caches, int wpr, int64_t slots) {
-    const int64_t natural = (int64_t)wpr * kTilesPerWave * kTile;
-    const int64_t nat = (ld + natural - 1) / natural;
-    const int64_t rounds = std::max<int64_t>(1, nat * caches / slots);
-    const int64_t chunks = std::max<int64_t>(1, rounds * slots / caches);
-    const int64_t per = (ld + chunks - 1) / chunks;                          // keys per chunk
-    const int64_t r = ((per + wpr - 1) / wpr + kTile - 1) / kTile * kTile;   // per wave, whole tiles
-    // At most three natural runs (chunks >= nat / 3 above); the bound keeps a
-    // run's bytes far inside the 32-bit range of its buffer resource.
-    const int run = (int)std::max<int64_t>(std::min<int64_t>(r, 4 * kTilesPerWave * kTile), kMinRun);
-    const int64_t grid = (ld + (int64_t)wpr * run - 1) / ((int64_t)wpr * run) * caches;
-    return {run, (double)grid / ((double)rounds * (double)slots)};
-}
-
 template <int H, int D, int RG>
 gvr_status launch(IdxParams q, int64_t caches, void* stream) {
-    // Key chunks per cache. The natural size gives every wave a run of
-    // kTilesPerWave tiles; the grid is then resized to whole rounds of m
-    // workgroups per compute unit: one round when the natural grid fits (small
-    // batches get finer chunks that reach more compute units, runs of at least
-    // kMinRun keys), else as many full rounds as it fills (no partly filled
-    // last round). m is the smallest from 2 on that the caches fill to nine
-    // tenths, else the best filled one: fewer workgroups with longer runs pay
-    // the queries and the first loads less often, and places left empty cost
-    // more than that. 40 x 1 rows of 20000 keys (H = 64, D = 128): 18.7 us at
-    // m = 2, 20.9 at 3, 21.3 at 4; 100 x 1 of 30000 50.9 / 57.1 / 57.2; 300 x 1
-    // of 3000, where m = 2 is 59 % full, 29.6 / 25.8 / 23.0.
-    //
-    // Where a cache's rows do not pair (groups of three, and H = 128), several
-    // waves read each key tile, and the reuse is the L1's. With D = 128 more
-    // than three such workgroups per compute unit evict each other's tiles, so
-    // unused LDS keeps it at three and the grid is cut for them (64 x 3 ragged
-    // rows of 60000 keys, H = 32: 135.9 us against 140.7 at four and 147.0
-    // unlimited); with D = 64 every resident workgroup counts (40 x 3 of 20000,
-    // H = 64: 26.5 against 32.5 at m = 2).
     const int wpr = q.chunk_keys / (kTilesPerWave * kTile);
-    const bool shared_tiles = RG == 1 && q.group > 1;
-    const bool limited = shared_tiles && D == 128;
-    int run = kTilesPerWave * kTile;
-    Resident res = resident_workgroups<H, D, RG>(stream);
-    if (res.per_cu > 0) {
-        double best = -1.0;
-        if (limited) res.per_cu = std::min(res.per_cu, kSharedPerCu);
-        for (int m = shared_tiles ? res.per_cu : std::min(2, res.per_cu); m <= res.per_cu && best < 0.9; ++m) {
-            const Cut c = cut_for(q.ld, caches, wpr, (int64_t)m * res.cus);
-            if (c.fill > best) {
-                best = c.fill;
-                run = c.run;
-            }
-        }
-    }
+    const Resident res = resident_workgroups<H, D, RG>(stream);
+    const gvr_idx::Grid plan = gvr_idx::plan_grid(q.ld, caches, wpr, res.per_cu, res.cus, RG == 1 && q.group > 1, D);
+    const int run = plan.run;
     q.run_keys = run;
     q.chunk_keys = wpr * run;
     const int64_t chunks = (q.ld + q.chunk_keys - 1) / q.chunk_keys;
     if (chunks * caches > 0x7FFFFFFF) return GVR_ERR_TOO_LONG;
     q.chunks = (int32_t)chunks;
     if (chunks * caches + (q.prev ? q.rows : 0) > 0x7FFFFFFF) return GVR_ERR_TOO_LONG;
+    q.rot = gvr_idx::rotation(plan, chunks, caches, q.row_len != nullptr);
     q.sample_base = (int32_t)(chunks * caches);   // the fused guess's workgroups follow the key chunks
     const unsigned grid = (unsigned)(chunks * caches + (q.prev ? q.rows : 0));
-    hipLaunchKernelGGL((indexer_kernel<H, D, RG>), dim3(grid), dim3(kWaves * kWave), limited ? kSharedLds : 0, (hipStream_t)stream,
+    hipLaunchKernelGGL((indexer_kernel<H, D, RG>), dim3(grid), dim3(kWaves * kWave), plan.limited ? kSharedLds : 0, (hipStream_t)stream,
                        q);
     return hipGetLastError() == hipSuccess ? GVR_OK : GVR_ERR_HIP;
 }

@@ -2,8 +2,8 @@
 // (g++ / gcc, no GPU code): the host-side planning of a Top-K call
 // (paper_2604_22312_amd/csrc/host_plan.h: argument checks, workgroup shape
 // and row split, workspace layout, the per-stream workspace cache with its
-// growth and keep-alive rule) and of the static prior (csrc/rope_plan.h), and
-// the C oracle (oracle/oracle_topk.c) against
+// growth and keep-alive rule), of the indexer's grid (csrc/indexer_plan.h) and
+// of the static prior (csrc/rope_plan.h), and the C oracle (oracle/oracle_topk.c) against
 // a brute-force full sort on tie-heavy rows with special values. Prints "ok".
 #include <stdio.h>
 #include <stdlib.h>
@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "host_plan.h"
+#include "indexer_plan.h"
 #include "rope_plan.h"
 
 extern "C" int oracle_topk(const float* scores, int64_t B, int64_t ld, const int32_t* row_len, int32_t K,
@@ -183,6 +184,55 @@ static void check_workspace() {
     g_capturing = false;
 }
 
+// The indexer's grid: runs of whole tiles that cover the rows, and every
+// chunk of a cache served once, whatever chunk the cache starts at.
+static void check_indexer_plan() {
+    using namespace gvr_idx;
+    for (int64_t ld : {1, 31, 3000, 33000, 131072})
+        for (int64_t caches : {1, 8, 300, 5000})
+            for (int wpr : {1, 2, 4})
+                for (int per_cu = 0; per_cu <= 5; ++per_cu)
+                    for (int shared = 0; shared < 2; ++shared)
+                        for (int D : {64, 128}) {
+                            const Grid g = plan_grid(ld, caches, wpr, per_cu, 256, shared, D);
+                            CHECK(g.run >= kMinRun && g.run <= 4 * kTilesPerWave * kTile && g.run % kTile == 0);
+                            CHECK(!g.limited || (shared && D == 128));
+                        }
+    // tiles shared by several waves: three workgroups per compute unit
+    CHECK(plan_grid(60000, 64, 1, 5, 256, true, 128).limited);
+    CHECK(!plan_grid(20000, 40, 1, 4, 256, true, 64).limited);
+    for (int64_t chunks = 1; chunks <= 200; ++chunks) {
+        const Grid g{1024, false, 512}, limited{1024, true, 768};
+        CHECK(rotation(g, chunks, 1000, false).mask == 0);
+        CHECK(rotation(g, chunks, 760 / chunks, true).mask == 0);   // one round
+        CHECK(rotation(limited, chunks, 1900 / chunks, true).mask == 0);   // two, of shared tiles
+        const Rotation r = rotation(g, chunks, 1000, true);
+        CHECK((chunks % 8 == 0) == (r.mask > 0) && (int64_t)r.mask * r.step < chunks && r.mask < kSpread);
+    }
+    // Ragged rows of a quarter to a whole stride: each of kSpread places in
+    // turn gets about its share of the chunks that hold keys.
+    std::mt19937 rng(3);
+    for (int64_t chunks : {8, 16, 24, 32, 40, 64, 96}) {
+        const Rotation r = rotation(Grid{1024, false, 512}, chunks, 3200, true);
+        std::vector<int> live(kSpread, 0);
+        int total = 0;
+        for (int64_t g = 0; g < 3200; ++g) {
+            const int64_t full = chunks / 4 + (int64_t)(rng() % (uint32_t)(chunks - chunks / 4)) + 1;
+            std::vector<int> seen(chunks, 0);
+            for (int64_t b = 0; b < chunks; ++b) {
+                int64_t c = b + first_chunk((int)g, r.shift, r.mask, r.step);   // as the kernel
+                if (c >= chunks) c -= chunks;
+                CHECK(c >= 0 && c < chunks && !seen[c]++);
+                if (c < full) {
+                    ++live[(g * chunks + b) % kSpread];
+                    ++total;
+                }
+            }
+        }
+        for (int v : live) CHECK(std::abs((double)v * kSpread / total - 1.0) < 0.1);
+    }
+}
+
 static void check_rope_plan() {
     using namespace gvr_rope;
     // every length the entry points take is one launch whose threads fit 32
@@ -287,6 +337,7 @@ int main() {
     check_validate();
     check_plans();
     check_workspace();
+    check_indexer_plan();
     check_rope_plan();
     check_lin_bin();
     check_binned_serves();

@@ -122,6 +122,13 @@ def test_indexer_grid_cut(requests, group, ld, H, D):
     test_indexer_grid_sizing(requests, group, ld, H, D)
 
 
+@pytest.mark.parametrize("requests,group,ld,H,D", [(300, 3, 9001, 32, 64)])
+def test_indexer_caches_start_at_other_chunks(requests, group, ld, H, D):
+    """Eight chunks per cache in two rounds of workgroups: with row lengths
+    given, the caches' workgroups start at different chunks."""
+    test_indexer_grid_sizing(requests, group, ld, H, D)
+
+
 def check_topk_exact(got, gpu_scores, rl, K, what):
     """The Top-K the call returned equals the oracle's Top-K over the very
     float32 scores the call wrote, on every row (bit-exact)."""
