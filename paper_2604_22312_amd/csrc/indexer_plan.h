@@ -22,6 +22,7 @@ constexpr int kSpread = 32;              // consecutive workgroups go to 8 XCDs 
 struct Cut {
     int run;
     double fill;
+    int64_t rounds, chunks;
 };
 inline Cut cut_for(int64_t ld, int64_t caches, int wpr, int64_t slots) {
     const int64_t natural = (int64_t)wpr * kTilesPerWave * kTile;
@@ -33,8 +34,8 @@ inline Cut cut_for(int64_t ld, int64_t caches, int wpr, int64_t slots) {
     // At most three natural runs (chunks >= nat / 3 above); the bound keeps a
     // run's bytes far inside the 32-bit range of its buffer resource.
     const int run = (int)std::max<int64_t>(std::min<int64_t>(r, 4 * kTilesPerWave * kTile), kMinRun);
-    const int64_t grid = (ld + (int64_t)wpr * run - 1) / ((int64_t)wpr * run) * caches;
-    return {run, (double)grid / ((double)rounds * (double)slots)};
+    const int64_t got = (ld + (int64_t)wpr * run - 1) / ((int64_t)wpr * run);
+    return {run, (double)(got * caches) / ((double)rounds * (double)slots), rounds, got};
 }
 
 struct Grid {
@@ -61,7 +62,12 @@ struct Grid {
 // more than three such workgroups per compute unit evict each other's tiles,
 // so the grid is cut for three and unused LDS keeps it there (64 x 3 ragged
 // rows of 60000 keys, H = 32: 135.9 us against 140.7 at four and 147.0
-// unlimited); with D = 64 every resident workgroup counts (40 x 3 of
+// unlimited). One round of two or more chunks per cache that leaves a tenth of
+// those places empty takes a larger m that fills better, without the limit
+// (200 x 3 of 6000, H = 32: 72.6 us in 78 % of three, 57.7 in 98 % of four; H = 64
+// 76.6 and 60.1); with one chunk per cache, or in more rounds, the limit
+// pays all the same (500 x 3 of 1500, H = 32: 36.4 us in 65 % of three, 40.7
+// in 98 % of four; 400 x 3 of 6000 112 in 87 %, 125); with D = 64 every resident workgroup counts (40 x 3 of
 // 20000, H = 64: 26.5 against 32.5 at m = 2).
 inline Grid plan_grid(int64_t ld, int64_t caches, int wpr, int per_cu, int cus, bool shared, int D) {
     const bool limit = shared && D == 128;
@@ -70,13 +76,13 @@ inline Grid plan_grid(int64_t ld, int64_t caches, int wpr, int per_cu, int cus, 
     double best = -1.0;
     int m = std::min(2, per_cu);
     if (shared) m = limit ? std::min(kSharedPerCu, per_cu) : per_cu;
-    const int most = limit ? m : per_cu;
-    for (; m <= most && best < 0.9; ++m) {
+    for (; m <= per_cu && best < 0.9; ++m) {
         const Cut c = cut_for(ld, caches, wpr, (int64_t)m * cus);
         if (c.fill > best) {
             best = c.fill;
             g = Grid{c.run, limit && m <= kSharedPerCu, (int64_t)m * cus};
         }
+        if (g.limited && (c.rounds > 1 || c.chunks == 1)) break;
     }
     return g;
 }

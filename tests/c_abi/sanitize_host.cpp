@@ -198,8 +198,13 @@ static void check_indexer_plan() {
                             CHECK(g.run >= kMinRun && g.run <= 4 * kTilesPerWave * kTile && g.run % kTile == 0);
                             CHECK(!g.limited || (shared && D == 128));
                         }
-    // tiles shared by several waves: three workgroups per compute unit
+    // tiles shared by several waves: three workgroups per compute unit, unless
+    // one round of several chunks per cache leaves places empty
     CHECK(plan_grid(60000, 64, 1, 5, 256, true, 128).limited);
+    CHECK(!plan_grid(3000, 300, 1, 5, 256, true, 128).limited && plan_grid(3000, 300, 1, 5, 256, true, 128).run < 1024);
+    CHECK(!plan_grid(6000, 200, 1, 4, 256, true, 128).limited && plan_grid(6000, 200, 1, 4, 256, true, 128).run < 1500);
+    CHECK(plan_grid(1500, 500, 1, 5, 256, true, 128).limited);   // one chunk per cache
+    CHECK(plan_grid(6000, 400, 1, 5, 256, true, 128).limited);   // three rounds
     CHECK(!plan_grid(20000, 40, 1, 4, 256, true, 64).limited);
     for (int64_t chunks = 1; chunks <= 200; ++chunks) {
         const Grid g{1024, false, 512}, limited{1024, true, 768};

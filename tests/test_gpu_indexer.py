@@ -122,6 +122,13 @@ def test_indexer_grid_cut(requests, group, ld, H, D):
     test_indexer_grid_sizing(requests, group, ld, H, D)
 
 
+@pytest.mark.parametrize("requests,group,ld,H,D", [(300, 3, 3000, 32, 128), (260, 3, 2500, 64, 128)])
+def test_indexer_short_rows_of_shared_tiles(requests, group, ld, H, D):
+    """Short rows whose waves share key tiles: more than three workgroups per
+    compute unit where those fill better."""
+    test_indexer_grid_sizing(requests, group, ld, H, D)
+
+
 @pytest.mark.parametrize("requests,group,ld,H,D", [(300, 3, 9001, 32, 64)])
 def test_indexer_caches_start_at_other_chunks(requests, group, ld, H, D):
     """Eight chunks per cache in two rounds of workgroups: with row lengths
