@@ -2567,10 +2567,9 @@ gvr_status run(const float* scores, int64_t B, int64_t ld, const int32_t* row_le
             if (st != GVR_OK) return st;
         }
     }
-    // Rows in launches of at most 2^24 (the grid holds 8 * chunk slots).
-    const int64_t kRowsPerLaunch = (int64_t)1 << 24;
-    for (int64_t r0 = 0; r0 < B; r0 += kRowsPerLaunch) {
-        const int64_t rows = std::min<int64_t>(B - r0, kRowsPerLaunch);
+    const int64_t most = gvr_host::rows_per_launch(plan);
+    for (int64_t r0 = 0; r0 < B; r0 += most) {
+        const int64_t rows = std::min<int64_t>(B - r0, most);
         const int64_t rows_pad = (rows + kXcds - 1) / kXcds * kXcds;
         Head h;
         h.scores = scores + r0 * ld;

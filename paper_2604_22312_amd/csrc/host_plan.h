@@ -191,6 +191,13 @@ inline gvr_status plan_call(int64_t B, int64_t ld, int32_t K, bool have_prev, co
     return GVR_OK;
 }
 
+// Rows of one launch: whole groups of kXcds rows, at most 2^24 (the grid holds
+// kXcds * chunk slots), and no more than a launch's threads fit in 32 bits.
+inline int64_t rows_per_launch(const Plan& p) {
+    const int64_t threads = (int64_t)p.shape * 64 * p.parts;   // of one row
+    return std::min<int64_t>((int64_t)1 << 24, (int64_t)0xFFFFFFFF / threads / kXcds * kXcds);
+}
+
 // ------------------------------------------------------------ split-row workspace
 // Layout for `slots` (row, part) slots: arrival words [rows <= slots] u64,
 // part counts [slots] i32, part thresholds [slots] u32, part histograms

@@ -123,6 +123,18 @@ static void check_plans() {
     // the secant search never splits
     o.secant = 1;
     CHECK(plan_call(8, 131079, 2048, true, o, 256, kMaxSlots, false, &p) == GVR_OK && p.parts == 1);
+    // rows of one launch: whole groups of 8, threads that fit 32 bits, and no
+    // launch smaller than it need be
+    for (int shape : {kNWShort, kNWMid, kNWLong})
+        for (int parts : {1, 2, 5, 16}) {
+            Plan q;
+            q.shape = shape;
+            q.parts = parts;
+            const int64_t rows = rows_per_launch(q);
+            CHECK(rows > 0 && rows % kXcds == 0 && rows <= ((int64_t)1 << 24));
+            CHECK(rows * parts * shape * 64 <= (int64_t)0xFFFFFFFF);
+            CHECK(rows + kXcds > ((int64_t)1 << 24) || (rows + kXcds) * parts * shape * 64 > (int64_t)0xFFFFFFFF);
+        }
     // choose_parts over many shapes stays within the compute units and the part limit
     for (int64_t rows = 1; rows <= 300; rows += 7)
         for (int64_t ld = 1000; ld <= 300000; ld = ld * 3 / 2) {

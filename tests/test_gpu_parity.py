@@ -584,6 +584,24 @@ def test_paper_refine_parity(case, flags):
                 assert 1 <= int(st["refine_iters"][r]) <= 64
 
 
+@pytest.mark.parametrize("rows,guess", [((1 << 23) + 9, True), ((1 << 24) + 9, False)],
+                         ids=["eight_waves_guess", "four_waves_radix"])
+def test_more_rows_than_a_launch_holds(rows, guess):
+    """Calls whose workgroups' threads exceed one launch's 2^32 - 1 are cut
+    into several launches: three elements per row, K = 1."""
+    import paper_2604_22312_amd as g
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows)
+    S = torch.rand((rows, 3), generator=gen, device=DEV)
+    prev = torch.zeros((rows, 1), dtype=torch.int32, device=DEV) if guess else None
+    note("gvr_topk rows=%d guess=%s" % (rows, guess))
+    out = g.gvr_topk(S, None, prev, 1)
+    torch.cuda.synchronize()
+    best = torch.where(S[:, 1] > S[:, 0], 1, 0)   # the lower index first among equals
+    best = torch.where(S[:, 2] > torch.maximum(S[:, 0], S[:, 1]), 2, best)
+    assert torch.equal(out[:, 0].long(), best)
+
+
 @pytest.mark.parametrize("ld,K", [(20001, 2048), (9999, 7), (70003, 1), (131071, 2000)])
 def test_paper_refine_special_rows(ld, K):
     import paper_2604_22312_amd as g
