@@ -12,12 +12,12 @@
 //   Guess (Sec. 4.2.1, Phase 1). Wave 0 of every part gathers the scores at a
 //   strided sample of prev_topk (every 8th entry for K = 2048, 256 in all)
 //   and reduces them to pmin / pmax / pmean and T_spec, the lower edge of the
-//   histogram bin (over [pmin, pmax]) holding the sampled key of rank
+//   bin (of 1024 over [pmin, pmax]) holding the sampled key of rank
 //   ceil(65 / 2048 * samples): a threshold the previous step's Top-K makes
 //   likely to leave a few thousand elements of the current row above it, so
 //   that K <= f(T_spec) <= C. Waves 1..15 have their first slabs (1 KB per
-//   wave: 64 lanes x one 16-byte load) in flight meanwhile and wait on an LDS
-//   flag, not a barrier, so a stalled load issue never delays T_spec.
+//   wave: 64 lanes x one 16-byte load) in flight meanwhile and wait for it on a
+//   word in LDS, not at a barrier, so a stalled load issue never delays T_spec.
 //
 //   Verify / collect (Sec. 4.2.2-4.2.3, Phases 2-3). One pass over the
 //   part's slabs counts f(T_spec) and appends every element at or above it
@@ -121,7 +121,7 @@ static_assert(Shape<kNWLong>::kCap == gvr_host::kCapLong && Shape<kNWMid>::kCap 
 static_assert(Shape<kNWLong>::kCap == GVR_MAX_CANDIDATES, "the long-row shape holds the largest capacity");
 static_assert(kPartCap == Shape<kNWLong>::kCap, "a workspace slot holds one part's lists");
 constexpr int kRefBins = 4096;                 // bins of a narrowing refine level (12 bits of key)
-constexpr int kRefBins1 = 2048;                // bins of the first refine level (32 per lane of one wave)
+constexpr int kRefBins1 = 2048;                // bins of the first refine level
 constexpr int kCoarse = kRefBins1 / 32;        // coarse bins of that level: one per lane
 constexpr int kDigitShift = 21;                // radix digit: the top 11 key bits, one first-level bin each
 static_assert(kGuessMaxK == GVR_MAX_K, "the T_spec quantile is taken over the largest K");
@@ -252,7 +252,7 @@ struct Smem {
     uint2 list[Shape<NW>::kCap];                   // candidates (key, index), in segments
     union alignas(16) {
         int hist[NW][kBinsX];          // wave-private counting histograms
-        int rhist[kRefBins];            // refine / guess histogram
+        int rhist[kRefBins];            // refine levels, digit histogram
     } u;
     int F[kBinsX + 1];                  // F[j] = f(edge j) over the row
     int seg_off[NW];
@@ -1152,7 +1152,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
         // blocks (lane offset clamped to the last block; refills past the
         // wave's share re-read its last slab, just fetched). Issuing them can
         // stall on a full memory pipeline, so the streaming waves do not meet
-        // wave 0 at a barrier afterwards: they poll the guess_ready flag right
+        // wave 0 at a barrier afterwards: they poll sm.guess right
         // before their first slab.
         const __amdgpu_buffer_rsrc_t rrow = row_rsrc(xa, nq * 16);
         const int lane16 = lane * 16, qlast16 = qlast * 16;
@@ -1172,7 +1172,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
             if (wave == 0) {
                 // ---------------- (a2) guess statistics (Sec. 4.2.1) over the
                 // sampled guessed scores: pmin, pmax, pmean, and T_spec = lower
-                // edge of the histogram bin (over [pmin, pmax]) holding the
+                // edge of the bin (of 1024 over [pmin, pmax]) holding the
                 // gathered key of rank ceil(65 * m / 2048) from the bottom.
                 // From the indexer, when it scored the sample (one load).
                 bool ok[4];
@@ -1219,7 +1219,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
         int stored_w = 0;   // entries listed when the list filled up
         uint2* lw = sm.list + wave * W::kCapW;
         // The streaming waves wait for T_spec here, with their first slabs in
-        // flight (polling an LDS flag, not a barrier: issuing those loads may
+        // flight (polling sm.guess, not at a barrier: issuing those loads may
         // stall a wave, which must not hold up wave 0).
         if (!all_mode) {
             uint64_t gword;
@@ -1322,7 +1322,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
 
         // Every wave turns its list into keys in place and adds them to the
         // refine's first histogram level over [T_spec, max(pmax, T_spec)]
-        // (cleared by wave 0 before its flag): waves done with their slabs
+        // (cleared by wave 0 before it publishes T_spec): waves done with their slabs
         // do this while the others still stream.
         keys_in_place(sm, lw, cnt_w <= W::kCapW ? cnt_w : stored_w, own_hist, tspec, hsh, lane);
         if (lane == 0) {

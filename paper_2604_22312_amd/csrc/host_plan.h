@@ -88,7 +88,8 @@ inline gvr_status validate(const void* scores, int64_t B, int64_t ld, int32_t K,
 }
 
 // Parts per row. Splitting a row over S workgroups divides its streaming
-// time (one workgroup reads about 33 GB/s on MI355X) but costs the merge of
+// time (one workgroup reads about 32 GB/s on MI355X from its first load to its
+// last, about 25 over a whole call) but costs the merge of
 // the parts' candidate lists, about 8 us of memory round trips when many
 // rows merge at once; split only when the time saved is larger, keep parts
 // >= kMinPartElems long and stay within the compute units. A call of one or

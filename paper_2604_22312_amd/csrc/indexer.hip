@@ -97,7 +97,7 @@ __device__ __forceinline__ v8i load32(const uint8_t* p) {
 // dimension per step), the key's scale, ReLU, the head weights wv (LDS,
 // float4 per lane quarter) and the sum over the lane's heads. The score is
 // (q0 + q1) + (q2 + q3) over the column's four lanes, in the main loop
-// (pair_scores) and in the fused guess (column_sum) alike, so a sampled key's
+// (use_slot) and in the fused guess (column_sum) alike, so a sampled key's
 // score equals the one written for it.
 template <int H>
 __device__ __forceinline__ float tile_quarter(const v8i (&qa)[H / 16], const v8i& kb, float ks, const float4* wv,

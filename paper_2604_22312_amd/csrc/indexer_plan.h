@@ -54,8 +54,11 @@ struct Grid {
 // and the first loads less often, and places left empty cost more than that.
 // 40 x 1 rows of 20000 keys (H = 64, D = 128): 18.7 us at m = 2, 20.9 at 3,
 // 21.3 at 4; 100 x 1 of 30000 50.9 / 57.1 / 57.2; 300 x 1 of 3000, where
-// m = 2 is 59 % full, 29.6 / 25.8 / 23.0. The rule is not the best m
-// everywhere: 8 x 1 of 131072 takes 25.7 us where m = 3 takes 24.1.
+// m = 2 is 59 % full, 29.6 / 25.8 / 23.0. It is not the best m everywhere:
+// 8 x 1 of 131072 takes 25.7 us where m = 3 takes 24.1, 16 x 1 ragged of
+// 70000 22.8 where m = 4 takes 20.6, 40 x 4 ragged of 20000 (H = 32) 32.6
+// where m = 3 takes 30.1; the places are counted from the stride, so ragged
+// rows fill fewer of them.
 //
 // Where a cache's rows do not pair (groups of three, and H = 128; `shared`),
 // several waves read each key tile, and the reuse is the L1's. With D = 128
@@ -64,11 +67,12 @@ struct Grid {
 // rows of 60000 keys, H = 32: 135.9 us against 140.7 at four and 147.0
 // unlimited). One round of two or more chunks per cache that leaves a tenth of
 // those places empty takes a larger m that fills better, without the limit
-// (200 x 3 of 6000, H = 32: 72.6 us in 78 % of three, 57.7 in 98 % of four; H = 64
-// 76.6 and 60.1); with one chunk per cache, or in more rounds, the limit
-// pays all the same (500 x 3 of 1500, H = 32: 36.4 us in 65 % of three, 40.7
-// in 98 % of four; 400 x 3 of 6000 112 in 87 %, 125); with D = 64 every resident workgroup counts (40 x 3 of
-// 20000, H = 64: 26.5 against 32.5 at m = 2).
+// (200 x 3 of 6000, H = 32: 72.6 us in 78 % of three, 57.7 in 98 % of four;
+// H = 64 76.6 and 60.1); with one chunk per cache, or in more rounds, the
+// limit pays all the same (500 x 3 of 1500, H = 32: 36.4 us in 65 % of three,
+// 40.7 in 98 % of four; 400 x 3 of 6000 112 in 87 %, 125). With D = 64 every
+// resident workgroup counts (40 x 3 of 20000, H = 64: 26.5 against 32.5 at
+// m = 2).
 inline Grid plan_grid(int64_t ld, int64_t caches, int wpr, int per_cu, int cus, bool shared, int D) {
     const bool limit = shared && D == 128;
     Grid g{kTilesPerWave * kTile, limit, 0};
@@ -97,9 +101,9 @@ inline Grid plan_grid(int64_t ld, int64_t caches, int wpr, int per_cu, int cus, 
 // 221 us, 256 x 4 (H = 32, D = 128) 281 -> 214, 300 x 1 (H = 64, D = 128)
 // 217 -> 187; equal lengths as before. A grid of one round has no place
 // waiting for another's chunks, and starting elsewhere costs locality (equal
-// lengths, H = 32, D = 128, 64 x 3 of 25000 in two
-// rounds, where tiles are shared: 77.8 -> 84.3), so it is done from two rounds
-// on, from three where tiles are shared. Other chunk counts spread by
+// lengths, H = 32, D = 128, 64 x 3 of 25000 in two rounds, where tiles are
+// shared: 77.8 -> 84.3 us), so it is done from two rounds on, from three where
+// tiles are shared. Other chunk counts spread by
 // themselves (300 x 3 ragged of 16384, D = 64, 12 chunks: 100.5 us, 124.6
 // rotated).
 struct Rotation {

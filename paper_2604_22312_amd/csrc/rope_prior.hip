@@ -12,9 +12,10 @@
 //   (1048576 positions 65.9 us with one lane each, 81.0 with four). Run once
 //   per model and length, not per decode step.
 //
-//   select kernel. One workgroup of 1024 threads, because the calls take no
-//   scratch memory that several could meet in; so it is bound by one compute
-//   unit's read rate and reads g twice. The first pass counts every element
+//   select kernel. One workgroup of 1024 threads: the calls take no scratch
+//   memory that several could meet in (only out_delta's K words are unused
+//   until the select writes them). So it is bound by one compute unit's read
+//   rate and reads g twice. The first pass counts every element
 //   into linear bins over [-d, d] (g cannot leave it), one histogram per wave:
 //   that gives the bin holding the K-th largest g and the place of each
 //   wave's elements at or above it. The second lists the indices of those, in
@@ -22,10 +23,10 @@
 //   among themselves (lower index first); a block scan writes the selected
 //   indices. (A radix select over the 64-bit keys read g four or five times
 //   with one load in flight: the prior of 131072 positions took 220 us, now
-//   46, of which the g kernel takes 14.) It remains for what
-//   the bins cannot serve (binned_serves of rope_plan.h says what is known
-//   ahead; the rest, NaN among it, is found by the first pass). Digits of 11, 11, 11, 11, 10, 10 bits of the
-//   order-preserving key; as soon as the elements sharing the selected prefix
+//   46, of which the g kernel takes 13.) It remains for what the bins cannot
+//   serve (binned_serves of rope_plan.h says what is known ahead; the rest,
+//   NaN among it, is found by the first pass). Digits of 11, 11, 11, 11, 10,
+//   10 bits of the order-preserving key; as soon as the elements sharing the selected prefix
 //   fit in LDS (<= 4096) they are gathered there; a final pass in index order
 //   writes the selection at offsets from two block scans per 4096 elements.
 
