@@ -157,12 +157,12 @@ constexpr int kGeoScatter = 5, kGeoStride = 6, kGeoSamples = 10;
 constexpr int kGeoFromIndexer = 19;   // the guess statistics come from the indexer (Params::gstats)
 constexpr int kGeoTimed = 20;         // row stats are asked for (Params::stats)
 constexpr int kGeoSecant = 21;        // the paper's Phase 2 (secant counting passes) instead of the speculative pass
-constexpr int kGeoPaperRefine = 22;   // the paper's Phase 4 (min/max, histogram, snap iterations) instead of refine_emit
 static_assert(kMaxParts < 32 && kGuessMaxK / kGuessSamples < 16 && kGuessSamples < 512, "fields of Head::geo");
 
 struct Params {
     int32_t* out;
     gvr_row_stats* stats;
+    int32_t paper_refine; // 1: the paper's Phase 4 (min/max, histogram, snap iterations) instead of refine_emit
     uint64_t* arrivals;  // [rows] parts that finished the speculative pass (S > 1), per XCD above
                          // bit 16; 0 between calls
     int32_t* part_count; // [rows][S] f(threshold) of each part, bit 31 = a wave list overflowed
@@ -605,6 +605,7 @@ DEV uint32_t paper_refine_emit(Smem<NW>& sm, int K, int32_t* out, int tid, int* 
         sm.red[2][wave] = (int)mn;
         sm.red[3][wave] = (int)mx;
     }
+    lds_barrier();   // a slower wave may still search these bins (bin_search)
     for (int i = tid; i < kPaperBins; i += W::kBlock) sm.u.rhist[i] = 0;
     lds_barrier();
     const uint32_t kmin = wave_min_u(lane < NW ? (uint32_t)sm.red[2][lane] : 0xFFFFFFFFu);
@@ -1109,7 +1110,6 @@ DEV void topk_body(const Head& hd, const Params& p) {
     bool have_prev = GUESS && hd.prev && !all_mode;
     // The paper's Phase 2 schedule (secant counting passes), when asked for.
     const bool secant = GUESS && ((hd.geo >> kGeoSecant) & 1u) && have_prev;
-    const bool paper_refine = (hd.geo >> kGeoPaperRefine) & 1u;   // does without the first level and its search
     const bool spec = (all_mode || have_prev) && !secant;
     int gvalid = 0;
     uint32_t gmax = 0u, tspec = 0xFFFFFFFFu;
@@ -1337,7 +1337,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
             gsum = sm.redf[0];
             if (gvalid == 0) have_prev = false;   // no usable guess: the pass kept (almost) nothing
         }
-        if (own_hist && S == 1 && !paper_refine) {
+        if (own_hist && S == 1) {
             // The level counts every key >= T_spec, full lists or not: its
             // total is f(T_spec), and the K-th key's bin follows from it.
             const int wc = lane < NW ? sm.wa[lane] : 0;
@@ -1613,7 +1613,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
                         sm.seg_cnt[tid] = min(chunk, f_spec - o);
                     }
                                     lds_barrier();   // every wave reads the merged list, its segment table and histogram after this
-                    if (!all_mode && !paper_refine) row_hit = bin_search(sm, sm.u.rhist, K, 0, tid);
+                    if (!all_mode) row_hit = bin_search(sm, sm.u.rhist, K, 0, tid);
                 }
             }
             // Ready for the next call (issued after the loads above).
@@ -1628,7 +1628,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
         const int64_t t3f = tstamp();
         int ngt = 0;
         int snaps = 0;
-        const uint32_t kth = paper_refine
+        const uint32_t kth = p.paper_refine
                                  ? paper_refine_emit(sm, K, out, tid, &ngt, &snaps)
                                  : refine_emit(sm, tthr, 0xFFFFFFFFu, max(gmax, tthr), 0, K, out, tid, &ngt,
                                                hist_ready ? &row_hit : nullptr);
@@ -2200,11 +2200,8 @@ DEV void topk_body(const Head& hd, const Params& p) {
             bin_hi = max(gmax, tthr);
             above = 0;
         } else if (spec && !secant && f_spec > cap && hist_full) {
-            BinHit bh = row_hit;   // searched already where the row has one part
-            if (S > 1 || paper_refine) {
-                __syncthreads();   // the level is complete
-                bh = bin_search(sm, sm.u.rhist, K, 0, tid);
-            }
+            __syncthreads();   // the level is complete
+            const BinHit bh = bin_search(sm, sm.u.rhist, K, 0, tid);
             const int b = bh.b, above_b = bh.above, cnt_b = bh.cnt;
             const uint32_t hsh = ref_shift(tthr, max(gmax, tthr));
             const uint64_t lo64 = (uint64_t)tthr + ((uint64_t)b << hsh);
@@ -2421,7 +2418,7 @@ DEV void topk_body(const Head& hd, const Params& p) {
     // ---------------- (a5) refine the listed candidates and emit
     int ngt = 0;
     int snaps = 0;
-    const uint32_t kth = paper_refine ? paper_refine_emit(sm, K, out, tid, &ngt, &snaps)
+    const uint32_t kth = p.paper_refine ? paper_refine_emit(sm, K, out, tid, &ngt, &snaps)
                                         : refine_emit(sm, rlo, rhi, bin_hi, above, K, out, tid, &ngt, nullptr);
     if (st && tid == 0) {
         gvr_row_stats s = {};
@@ -2583,11 +2580,11 @@ gvr_status run(const float* scores, int64_t B, int64_t ld, const int32_t* row_le
         h.s_magic = (uint32_t)(((1ull << 32) + (uint64_t)parts - 1) / (uint64_t)parts);
         h.geo = (uint32_t)parts | (uint32_t)o.scatter << kGeoScatter | (uint32_t)guess_stride(K) << kGeoStride |
                 (uint32_t)guess_count(K) << kGeoSamples | (uint32_t)(guess && gstats ? 1 : 0) << kGeoFromIndexer |
-                (uint32_t)(stats ? 1 : 0) << kGeoTimed | (uint32_t)(o.secant ? 1 : 0) << kGeoSecant |
-                (uint32_t)(o.paper_refine ? 1 : 0) << kGeoPaperRefine;
+                (uint32_t)(stats ? 1 : 0) << kGeoTimed | (uint32_t)(o.secant ? 1 : 0) << kGeoSecant;
         Params q;
         q.out = out + r0 * K;
         q.stats = stats ? stats + r0 : nullptr;
+        q.paper_refine = o.paper_refine;
         q.arrivals = ws.arrivals;
         q.part_count = ws.part_count;
         q.part_thresh = ws.part_thresh;
