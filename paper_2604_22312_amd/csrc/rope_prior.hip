@@ -23,7 +23,7 @@
 //   among themselves (lower index first); a block scan writes the selected
 //   indices. (A radix select over the 64-bit keys read g four or five times
 //   with one load in flight: the prior of 131072 positions took 220 us, now
-//   46, of which the g kernel takes 13.) It remains for what the bins cannot
+//   46, of which the g kernel takes 14.) It remains for what the bins cannot
 //   serve (binned_serves of rope_plan.h says what is known ahead; the rest,
 //   NaN among it, is found by the first pass). Digits of 11, 11, 11, 11, 10,
 //   10 bits of the order-preserving key; as soon as the elements sharing the selected prefix
